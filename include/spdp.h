@@ -334,7 +334,9 @@ int spdp_max_sources(const spdp_state *s, int32_t *S);
  * weights per token, every token draws (no -1), and zr_out holds
  * s << 16 | 2 z + r.  With w_out and u_out both NULL no trace is kept and
  * any token range may be requested (the sampled state before the count update
- * and repair).  Uses the same kernel as spdp_sweep.  Synchronises.
+ * and repair) from spdp_sweep's own kernel; with a trace the step runs on the
+ * kernel over count rows, which forms every outcome's weight and draws the
+ * same outcomes.  Synchronises.
  * Errors: E_ARG, E_NOMEM, E_HIP.
  */
 int spdp_debug_conditionals(spdp_state *s, uint32_t sweep, uint64_t seed, int64_t tok_begin,
@@ -351,9 +353,11 @@ int spdp_stats(const spdp_state *s, int64_t *changed, int64_t *repaired);
  * Per-kernel timing with HIP events on the state's stream.  enable = 1 starts
  * recording (and clears the accumulators), 0 stops.  spdp_kernel_times writes
  * the accumulated milliseconds and launch counts of the SPDP_NKERNELS kernel
- * classes, in this order: sampling; count rebuild with repair (which also
- * sums the shadow-base counts); the 16-bit copy of the shadow base;
- * per-restaurant totals and per-sweep constants.  Synchronises.
+ * classes, in this order: sampling (with the weight rows, where the state
+ * samples from them); count rebuild with repair (which also sums the
+ * shadow-base counts); the 16-bit copy of the shadow base (only for states
+ * that sample from count rows); per-restaurant totals and per-sweep
+ * constants.  Synchronises.
  */
 #define SPDP_NKERNELS 4
 int spdp_kernel_timing(spdp_state *s, int enable);

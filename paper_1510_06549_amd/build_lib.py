@@ -13,7 +13,8 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["api.hip", "setup.hip", "counts.hip", "sample.hip", "sample_assoc.hip", "sample_async.hip",
+SOURCES = ["api.hip", "setup.hip", "counts.hip", "sample.hip", "sample_assoc.hip",
+           "sample_rows.hip", "sample_rows_assoc.hip", "sample_async.hip",
            "loglik.hip",
            "estimate.hip",
            "hellinger.hip",

@@ -57,6 +57,9 @@ struct spdp_state {
     // true while the 32-bit rows of the narrow rows equal their 16-bit copies
     // (the rebuild writes a narrow row only as its copy)
     mutable bool rows32 = false;
+    // true while the 16-bit copy of the shadow base and its width flag match B
+    // (the sampler over weight rows does not read them)
+    bool base16 = false;
     bool timing = false;
     std::vector<EventPair> events[SPDP_NKERNELS];
     std::vector<void *> allocs;
@@ -135,7 +138,7 @@ int rebuild_state(spdp_state *s)
     int32_t *zr = b.zr[s->cur];
     if (m.Sp > 0) HIP_TRY(launch_rows_assoc(m, b, zr, s->st));
     else HIP_TRY(launch_rows(m, b, zr, s->st));
-    HIP_TRY(launch_base16(m, b, s->st));
+    s->base16 = false;
     s->rows32 = false;
     HIP_TRY(launch_totals(m, b, zr, s->st));
     if (m.N > 0)
@@ -153,6 +156,35 @@ hipError_t widen_rows(const spdp_state *s)
     hipError_t e = launch_widen(s->m, s->b, s->st);
     if (e == hipSuccess) s->rows32 = true;
     return e;
+}
+
+// The 16-bit copy of the shadow base, once after each rebuild, for the samplers
+// over count rows and the invariant check.
+hipError_t copy_base16(spdp_state *s)
+{
+    if (s->base16) return hipSuccess;
+    hipError_t e = launch_base16(s->m, s->b, s->st);
+    if (e == hipSuccess) s->base16 = true;
+    return e;
+}
+
+// The sampling step of one sweep, from the sweep-start counts (constants
+// already computed): over weight rows where the state has them.
+hipError_t sample_step(spdp_state *s, const int32_t *zr_old, int32_t *zr_new, uint32_t sweep,
+                       uint64_t seed)
+{
+    const Model &m = s->m;
+    const DeviceBuffers &b = s->b;
+    hipError_t e;
+    if (m.rows.Kw > 0) {
+        if ((e = launch_weights(m, b, s->st)) != hipSuccess) return e;
+        return launch_sample_rows(m, b, zr_old, zr_new, sweep, seed, s->st);
+    }
+    if ((e = copy_base16(s)) != hipSuccess) return e;
+    if (m.Sp > 0)
+        return launch_sample_assoc(m, b, zr_old, zr_new, sweep, seed, nullptr, nullptr, 0, 0,
+                                   s->st);
+    return launch_sample(m, b, zr_old, zr_new, sweep, seed, nullptr, nullptr, 0, 0, s->st);
 }
 
 int check_device_flags(spdp_state *s, int32_t *host_err)
@@ -402,7 +434,7 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
     // tokens grouped by count row (the count rebuild walks rows); the rows
     // whose (group, word) pair occurs at most kNarrowMax times (fixed by the
     // corpus) also get 16-bit copies
-    unsigned long long n_narrow = 0;
+    unsigned long long n_rows[2] = {0, 0};  // narrow rows, rows that have tokens
     {
         int rc2 = dev_alloc(s, &B.perm, N, "row-sorted tokens");
         if (!assoc) {  // the plain model's rebuild gathers from routed states
@@ -420,12 +452,12 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         if (e == hipSuccess)
             e = launch_narrow_flags(m, B.gw, gw_count, B.row_narrow, B.tok_narrow, B.ctr, s->st);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(&n_narrow, B.ctr, sizeof n_narrow, hipMemcpyDeviceToHost, s->st);
+            e = hipMemcpyAsync(n_rows, B.ctr, sizeof n_rows, hipMemcpyDeviceToHost, s->st);
         if (e == hipSuccess) e = hipStreamSynchronize(s->st);
         cleanup_staging();
         TRY_HIP(e);
     }
-    s->n_narrow_rows = (int64_t)n_narrow;
+    s->n_narrow_rows = (int64_t)n_rows[0];
 
     // word associations
     if (assoc) TRY(upload_assoc(s, assoc));
@@ -455,7 +487,7 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
     // sits at q Kp; only the narrow rows' copies are written and read; the
     // sampler's vector reads of a narrow row run at most 4 cells past its
     // end, which the 64-cell tail keeps inside the buffer)
-    const int64_t n16 = (n_narrow > 0 ? rows * m.Kp : 0) + 64;
+    const int64_t n16 = (n_rows[0] > 0 ? rows * m.Kp : 0) + 64;
     TRY(dev_alloc(s, &B.nt16, n16, "narrow count rows"));
     TRY_HIP(launch_fill_i32(reinterpret_cast<int32_t *>(B.nt16), n16 / 2, 0, s->st));
     TRY(dev_alloc(s, &B.Ngk, (int64_t)G * m.Kp, "N_gk"));
@@ -464,6 +496,14 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
     TRY(dev_alloc(s, &B.f0, (int64_t)G * m.Kp, "f0"));
     TRY(dev_alloc(s, &B.f1, (int64_t)G * m.Kp, "f1"));
     TRY(dev_alloc(s, &B.fk, 3 * (int64_t)G * m.Kp, "removal factors"));
+    m.rows = row_shape(N, D, rows, (int64_t)n_rows[1], K);
+    if (m.rows.Kw > 0) {
+        TRY(dev_alloc(s, &B.pw, rows * m.rows.Kw, "weight rows"));
+        TRY(dev_alloc(s, &B.rho, rows * m.rows.Kw, "weight rows"));
+        TRY(dev_alloc(s, &B.fz, 2 * (int64_t)G * m.Kp, "topic constants"));
+        TRY(dev_alloc(s, &B.order_len, D, "document order"));
+        TRY_HIP(launch_doc_order(m, B.doc_off, B.order_len, s->st));
+    }
     TRY(dev_alloc(s, &B.rep_part, rows, "repair partial counts"));
     TRY(dev_alloc(s, &B.part, stat_partials_needed(), "reduction partials"));
     {
@@ -485,6 +525,10 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         x.srcrec = B.srcrec;
         x.p64 = B.p64;
         x.Sp = m.Sp;
+        x.Kp = m.Kp;
+        x.nt = B.nt;
+        x.nt16 = B.nt16;
+        x.row_narrow = B.row_narrow;
         TRY_HIP(hipMemcpyAsync(B.exact, &x, sizeof x, hipMemcpyHostToDevice, s->st));
         TRY_HIP(hipStreamSynchronize(s->st));
     }
@@ -515,26 +559,16 @@ int spdp_sweep(spdp_state *s, uint32_t sweep, uint64_t seed)
     int32_t *zr_old = b.zr[s->cur], *zr_new = b.zr[1 - s->cur];
     int rc;
     if ((rc = timed(s, 3, [&] { return launch_factors(m, b, s->st); })) != SPDP_OK) return rc;
-    if (m.Sp > 0) {
-        // word associations: source-keyed shadow base, rebuilt by the row pass
-        if ((rc = timed(s, 0, [&] {
-                 return launch_sample_assoc(m, b, zr_old, zr_new, sweep, seed, nullptr, nullptr,
-                                            0, 0, s->st);
-             })) != SPDP_OK)
-            return rc;
-        if ((rc = timed(s, 1, [&] { return launch_rows_assoc(m, b, zr_new, s->st); })) != SPDP_OK)
-            return rc;
-        if ((rc = timed(s, 2, [&] { return launch_base16(m, b, s->st); })) != SPDP_OK) return rc;
-    } else {
-        if ((rc = timed(s, 0, [&] {
-                 return launch_sample(m, b, zr_old, zr_new, sweep, seed, nullptr, nullptr, 0, 0,
-                                      s->st);
-             })) != SPDP_OK)
-            return rc;
-        if ((rc = timed(s, 1, [&] { return launch_rows(m, b, zr_new, s->st); })) != SPDP_OK)
-            return rc;
-        if ((rc = timed(s, 2, [&] { return launch_base16(m, b, s->st); })) != SPDP_OK) return rc;
-    }
+    if ((rc = timed(s, 0, [&] { return sample_step(s, zr_old, zr_new, sweep, seed); })) != SPDP_OK)
+        return rc;
+    // (word associations: source-keyed shadow base)
+    if ((rc = timed(s, 1, [&] {
+             return m.Sp > 0 ? launch_rows_assoc(m, b, zr_new, s->st)
+                             : launch_rows(m, b, zr_new, s->st);
+         })) != SPDP_OK)
+        return rc;
+    s->base16 = false;
+    if (m.rows.Kw == 0 && (rc = timed(s, 2, [&] { return copy_base16(s); })) != SPDP_OK) return rc;
     s->rows32 = false;
     if ((rc = timed(s, 3, [&] { return launch_totals(m, b, zr_new, s->st); })) != SPDP_OK) return rc;
     s->cur = 1 - s->cur;
@@ -579,7 +613,8 @@ int spdp_sweep_async(spdp_state *s, uint32_t sweep, uint64_t seed, int32_t waves
          })) != SPDP_OK)
         return rc;
     if ((rc = timed(s, 1, [&] { return launch_rows(m, b, zr_new, s->st); })) != SPDP_OK) return rc;
-    if ((rc = timed(s, 2, [&] { return launch_base16(m, b, s->st); })) != SPDP_OK) return rc;
+    s->base16 = false;
+    if (m.rows.Kw == 0 && (rc = timed(s, 2, [&] { return copy_base16(s); })) != SPDP_OK) return rc;
     s->rows32 = false;
     if ((rc = timed(s, 3, [&] { return launch_totals(m, b, zr_new, s->st); })) != SPDP_OK) return rc;
     s->cur = 1 - s->cur;
@@ -1043,12 +1078,18 @@ int spdp_debug_conditionals(spdp_state *s, uint32_t sweep, uint64_t seed, int64_
     }
     int32_t *zr_old = b.zr[s->cur], *zr_tmp = b.zr_dbg;
     HIP_TRY(launch_factors(m, b, s->st));
-    if (m.Sp > 0)
-        HIP_TRY(launch_sample_assoc(m, b, zr_old, zr_tmp, sweep, seed, trace ? b.tr_w : nullptr,
-                                    trace ? b.tr_u : nullptr, tok_begin, tok_end, s->st));
-    else
-        HIP_TRY(launch_sample(m, b, zr_old, zr_tmp, sweep, seed, trace ? b.tr_w : nullptr,
-                              trace ? b.tr_u : nullptr, tok_begin, tok_end, s->st));
+    if (!trace) {
+        HIP_TRY(sample_step(s, zr_old, zr_tmp, sweep, seed));
+    } else {
+        // the samplers over count rows form every outcome's weight
+        HIP_TRY(copy_base16(s));
+        if (m.Sp > 0)
+            HIP_TRY(launch_sample_assoc(m, b, zr_old, zr_tmp, sweep, seed, b.tr_w, b.tr_u,
+                                        tok_begin, tok_end, s->st));
+        else
+            HIP_TRY(launch_sample(m, b, zr_old, zr_tmp, sweep, seed, b.tr_w, b.tr_u, tok_begin,
+                                  tok_end, s->st));
+    }
     const hipMemcpyKind kind = where ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     if (w_out) HIP_TRY(hipMemcpyAsync(w_out, b.tr_w, (size_t)(T * nout) * 4, kind, s->st));
     if (u_out) HIP_TRY(hipMemcpyAsync(u_out, b.tr_u, (size_t)T * 4, kind, s->st));
@@ -1159,6 +1200,7 @@ int spdp_check(spdp_state *s, int64_t *bad)
     }
     unsigned long long c[4] = {0, 0, 0, 0};
     hipError_t e = launch_fill_u64(s->b.ctr, 4, 0, s->st);
+    if (e == hipSuccess) e = copy_base16(s);
     if (e == hipSuccess) e = launch_check(m, s->b, s->b.zr[s->cur], scratch, s->b.ctr, s->st);
     if (e == hipSuccess) e = hipMemcpyAsync(c, s->b.ctr, sizeof c, hipMemcpyDeviceToHost, s->st);
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);

@@ -79,7 +79,9 @@ __global__ void k_row_narrow(int64_t rows, const int32_t *__restrict__ gw_count,
     const bool nar = q < rows && gw_count[q] <= kNarrowMax;
     if (q < rows) row_narrow[q] = nar ? 1 : 0;
     const unsigned long long c = __popcll(__ballot(nar));
+    const unsigned long long u = __popcll(__ballot(q < rows && gw_count[q] > 0));
     if ((threadIdx.x & 63) == 0 && c) atomicAdd(n, c);
+    if ((threadIdx.x & 63) == 0 && u) atomicAdd(n + 1, u);
 }
 
 __global__ void k_tok_narrow(int64_t N, const int32_t *__restrict__ gw,
@@ -302,33 +304,39 @@ __global__ void k_topic_tables(int32_t G, int32_t Kp, const int32_t *__restrict_
 //   fk[0] = 1 / (b + N - 1)
 //   fk[1] = (b + a T) / (b + N - 1) / (V gamma + B_k)            (r = 0 removed)
 //   fk[2] = (b + a (T - 1)) / (b + N - 1) / (V gamma + B_k - 1)  (r = 1 removed)
-// Padding topics (k >= K) get 0, so their outcomes carry zero weight.
+// Padding topics (k >= K) get 0, so their outcomes carry zero weight.  fz (may
+// be null) holds the same five per topic: {fk[0], fk[1], fk[2], 0}, {f0, f1, 0, 0}.
 __global__ void k_factors(int32_t G, int32_t K, int32_t Kp, double a, double b, double Vgamma,
                           const int32_t *__restrict__ Ngk, const int32_t *__restrict__ Tgk,
                           const int32_t *__restrict__ Bk, float *__restrict__ f0,
-                          float *__restrict__ f1, float *__restrict__ fk)
+                          float *__restrict__ f1, float *__restrict__ fk,
+                          float4 *__restrict__ fz)
 {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t GK = (int64_t)G * Kp;
     if (j >= GK) return;
     const int32_t k = (int32_t)(j % Kp);
-    if (k >= K) {
-        f0[j] = f1[j] = 0.0f;
-        fk[j] = fk[GK + j] = fk[2 * GK + j] = 0.0f;
-        return;
+    float c0 = 0.0f, c1 = 0.0f, d0 = 0.0f, d1 = 0.0f, d2 = 0.0f;
+    if (k < K) {
+        const double N = (double)Ngk[j], T = (double)Tgk[j], B = (double)Bk[k];
+        const double inv = 1.0 / (b + N);
+        c0 = (float)inv;
+        c1 = (float)((b + a * T) * inv / (Vgamma + B));
+        if (Ngk[j] >= 1) {
+            const double invm = 1.0 / (b + N - 1.0);
+            d0 = (float)invm;
+            d1 = (float)((b + a * T) * invm / (Vgamma + B));
+            if (Tgk[j] >= 1) d2 = (float)((b + a * (T - 1.0)) * invm / (Vgamma + B - 1.0));
+        }
     }
-    const double N = (double)Ngk[j], T = (double)Tgk[j], B = (double)Bk[k];
-    const double inv = 1.0 / (b + N);
-    f0[j] = (float)inv;
-    f1[j] = (float)((b + a * T) * inv / (Vgamma + B));
-    if (Ngk[j] >= 1) {
-        const double invm = 1.0 / (b + N - 1.0);
-        fk[j] = (float)invm;
-        fk[GK + j] = (float)((b + a * T) * invm / (Vgamma + B));
-        fk[2 * GK + j] =
-            Tgk[j] >= 1 ? (float)((b + a * (T - 1.0)) * invm / (Vgamma + B - 1.0)) : 0.0f;
-    } else {
-        fk[j] = fk[GK + j] = fk[2 * GK + j] = 0.0f;
+    f0[j] = c0;
+    f1[j] = c1;
+    fk[j] = d0;
+    fk[GK + j] = d1;
+    fk[2 * GK + j] = d2;
+    if (fz) {
+        fz[2 * j] = make_float4(d0, d1, d2, 0.0f);
+        fz[2 * j + 1] = make_float4(c0, c1, 0.0f, 0.0f);
     }
 }
 
@@ -473,7 +481,7 @@ hipError_t launch_factors(const Model &m, const DeviceBuffers &b, hipStream_t st
     const int64_t n = (int64_t)m.G * m.Kp;
     hipLaunchKernelGGL(k_factors, dim3((unsigned)blocks_for(n, kBlock)), dim3(kBlock), 0, st, m.G,
                        m.K, m.Kp, m.a, m.b, (double)m.V * m.gamma, b.Ngk, b.Tgk, b.Bk, b.f0, b.f1,
-                       b.fk);
+                       b.fk, b.fz);
     return hipGetLastError();
 }
 

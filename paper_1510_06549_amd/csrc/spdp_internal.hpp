@@ -104,6 +104,13 @@ __host__ __device__ __forceinline__ int32_t wide_of(uint32_t cell16)
     return (int32_t)((cell16 & 0xFFu) | ((cell16 & 0xFF00u) << 8));
 }
 
+// Shape of the sampler over weight rows: lanes per document, topics per lane,
+// and the stored length of a weight row (Kw = 0: the state samples from its
+// count rows instead).
+struct RowShape {
+    int32_t lanes = 0, kpl = 0, Kw = 0;
+};
+
 struct Model {
     int64_t N;
     int32_t D, V, G, K, Kp;
@@ -114,6 +121,7 @@ struct Model {
     // word associations (0 for the plain model, P = I): S = longest source
     // list, Sp = S rounded up to 1, 2, 4 or 8 (the slot count of the records)
     int32_t S = 0, Sp = 0;
+    RowShape rows;
 };
 
 // Inputs of the sampler's rare fp64 re-decision path, kept in device memory
@@ -128,6 +136,11 @@ struct ExactCtx {
     const int32_t *srcrec;
     const double *p64;
     int32_t Sp;
+    // count rows, for the sampler over weight rows
+    int32_t Kp;
+    const int32_t *nt;
+    const uint16_t *nt16;
+    const uint8_t *row_narrow;
 };
 
 struct DeviceBuffers {
@@ -162,6 +175,13 @@ struct DeviceBuffers {
     float *f1 = nullptr;          // [G][Kp] (b + a T_gk) / (b + N_gk) / (V gamma + B_k)
     float *fk = nullptr;          // [3][G][Kp] the same with one customer removed:
                                   //   1/(b + N - 1), and f1 for a removed non-head / head
+    float4 *fz = nullptr;         // [G][Kp][2] the same constants topic by topic:
+                                  //   fk[0], fk[1], fk[2], 0, f0, f1, 0, 0
+    float *pw = nullptr;          // [G V][Kw] weight rows: both outcomes of a topic together
+                                  // (rewritten every sweep for the rows that have tokens;
+                                  // see sample_rows.hpp)
+    float *rho = nullptr;         // [G V][Kw] the share of the r = 1 outcome in each
+    int32_t *order_len = nullptr; // [D] documents in the launch order of that sampler
     float2 *Q = nullptr;          // [tri(ncap)] (Q0, Q1) folded Stirling ratios
     double *logS = nullptr;       // [tri(ncap + 1)] log S^n_{t,a}
     double2 *Q64 = nullptr;       // [tri(ncap)] the ratio pairs in fp64
@@ -204,7 +224,8 @@ hipError_t launch_make_gw(const Model &m, const int32_t *words, const int64_t *d
                           int32_t *bad, hipStream_t st);
 hipError_t launch_max_i32(const int32_t *x, int64_t n, int32_t *out, hipStream_t st);
 // narrow-row flags from the per-row token counts: per row and per token; the
-// number of narrow rows is added to *n_narrow
+// number of narrow rows is added to n_narrow[0], that of rows with tokens to
+// n_narrow[1]
 hipError_t launch_narrow_flags(const Model &m, const int32_t *gw, const int32_t *gw_count,
                                uint8_t *row_narrow, uint8_t *tok_narrow,
                                unsigned long long *n_narrow, hipStream_t st);
@@ -255,6 +276,16 @@ hipError_t launch_sample(const Model &m, const DeviceBuffers &b, const int32_t *
 hipError_t launch_sample_assoc(const Model &m, const DeviceBuffers &b, const int32_t *zr_old,
                                int32_t *zr_new, uint32_t sweep, uint64_t seed, float *tr_w,
                                float *tr_u, int64_t tr_begin, int64_t tr_end, hipStream_t st);
+// sampler over weight rows: the shape for a state (Kw = 0: none; rows_used:
+// count rows that have tokens), the documents'
+// launch order, the weight rows of the current counts and constants, and the
+// sampling step
+RowShape row_shape(int64_t N, int32_t D, int64_t rows, int64_t rows_used, int32_t K);
+hipError_t launch_doc_order(const Model &m, const int64_t *doc_off, int32_t *order,
+                            hipStream_t st);
+hipError_t launch_weights(const Model &m, const DeviceBuffers &b, hipStream_t st);
+hipError_t launch_sample_rows(const Model &m, const DeviceBuffers &b, const int32_t *zr_old,
+                              int32_t *zr_new, uint32_t sweep, uint64_t seed, hipStream_t st);
 hipError_t launch_loglik(const Model &m, const DeviceBuffers &b, const int32_t *zr,
                          hipStream_t st);
 // asynchronous sweep: token -> document and position, the visiting order

@@ -1,0 +1,63 @@
+"""The sampler over weight rows at the edges of its shapes, against the oracle.
+
+The lanes per document follow the number of documents (16 above 32 768, 32 or
+64 below), the topics per lane the topic count; chunks hold 16 tokens.  The
+small-corpus tests elsewhere reach the 32- and 64-lane instances at every
+topic count; these corpora have enough documents for the 16-lane ones, with
+lengths around whole chunks, empty documents, and (K = 520) a lane layout with
+a remainder at 64 lanes.  The bounds are the parity protocol's.
+"""
+import numpy as np
+import pytest
+
+import synth
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _corpus(docs, K, seed):
+    """`docs` documents in 3 groups: lengths mostly 0 to 3, some around the
+    chunk edges; 150 words with a Zipf law each group permutes."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 4, docs)
+    edge = rng.choice(docs, 400, replace=False)
+    lens[edge] = rng.choice([15, 16, 17, 31, 32, 33, 48, 70], 400)
+    off = np.zeros(docs + 1, dtype=np.int64)
+    np.cumsum(lens, out=off[1:])
+    group = np.sort(rng.integers(0, 3, docs)).astype(np.int32)
+    V = 150
+    law = 1.0 / np.arange(1, V + 1)
+    w = rng.choice(V, size=int(off[-1]), p=law / law.sum())
+    w = (w + 41 * np.repeat(group, lens)) % V
+    z = np.zeros(int(off[-1]), dtype=np.int32)
+    return synth.Corpus(w.astype(np.int32), off, group, z, z.astype(np.uint8), 3, V)
+
+
+@pytest.mark.parametrize("docs,K", [(33000, 1), (33000, 16), (33000, 17), (33000, 60),
+                                    (33000, 112), (33000, 144), (33000, 208), (33000, 256),
+                                    (3000, 130), (3000, 520)])
+def test_sweeps_match_oracle_at_every_lane_layout(docs, K):
+    print(f"weight rows: docs={docs} K={K}", flush=True)
+    cp = _corpus(docs, K, 100 * K + docs % 97)
+    wl = synth.workload(0)
+    s, m = parity.make_pair(cp, wl, K=K)
+    for sweep in range(2):
+        rep, _, _ = parity.one_step(s, m, sweep, 77)
+        assert rep.mismatches == 0
+    s.check()
+    s.close()
+
+
+@pytest.mark.parametrize("docs,K,S", [(33000, 40, 3), (33000, 200, 8), (3000, 70, 1)])
+def test_sweeps_with_associations_match_oracle(docs, K, S):
+    print(f"weight rows: docs={docs} K={K} sources={S}", flush=True)
+    cp = _corpus(docs, K, 7 * K + S)
+    wl = synth.workload(0)
+    assoc = synth.associations(3, cp.vocab, S, 0.3 if S > 1 else 0.0, 5)
+    s, m = parity.make_pair(cp, wl, K=K, assoc=assoc)
+    for sweep in range(2):
+        rep, _, _ = parity.one_step(s, m, sweep, 78)
+        assert rep.mismatches == 0
+    s.check()
+    s.close()
