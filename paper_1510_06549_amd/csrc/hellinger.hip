@@ -8,9 +8,9 @@
 //   BC(p, q)  = sum_v sqrt(p_v) sqrt(q_v)      (Bhattacharyya coefficient),
 // so all kp x kq coefficients are one dense contraction over the outcomes,
 //   BC = sqrt(P)^T sqrt(Q),   P [V][kp], Q [V][kq]  (topics contiguous),
-// which runs on the fp64 matrix cores: v_mfma_f64_16x16x4 blocks, 64 x 64
-// output tiles per 256-thread block, 16 outcomes staged per step through LDS
-// with the square roots taken once per staged value.  The outcome axis is
+// which runs on the fp64 matrix cores: v_mfma_f64_16x16x4 blocks, 64 x 64 or
+// 128 x 128 output tiles per 256-thread block, 16 outcomes staged per step
+// through LDS with the square roots taken once per staged value.  The outcome axis is
 // split into slices so that the grid fills the chip even for small K; the
 // slices' partial sums are added in slice order (deterministic) and
 // H = sqrt(max(0, 1 - BC)).
@@ -38,60 +38,104 @@ static __device__ __align__(256) double scratch[kHellingerScratch];
 
 namespace {
 
-constexpr int kTile = 64;     // output tile: kTile x kTile coefficients
+constexpr int kTile = 64;     // output tile of the plan's unit: kTile x kTile coefficients
 constexpr int kStage = 16;    // outcomes per LDS stage (4 MFMA k-steps)
-constexpr int kPad = 2;       // LDS row padding (doubles)
-constexpr int kThreads = 256; // 4 waves, each a 32 x 32 quarter of the tile
+constexpr int kThreads = 256; // 4 waves, each a quarter of the tile
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-// part[s][i][j] = sum over outcomes v of slice s of sqrt(P[v][i]) sqrt(Q[v][j])
+// part[s][i][j] = sum over outcomes v of slice s of sqrt(P[v][i]) sqrt(Q[v][j]),
+// for one TILE x TILE tile per block, each wave a quarter of it as NB x NB
+// matrix-core blocks.  A stage's values are requested before the stage before
+// it is multiplied, their square roots taken after it and written to the other
+// LDS buffer, so one barrier per stage suffices and neither the loads' latency
+// nor the square roots of one wave leave the matrix cores waiting.  The square
+// roots (about 90 cycles each) are the competitor: a 64 x 64 tile takes 8 per
+// thread and 16 MFMAs (64 cycles each) per stage, a 128 x 128 tile 16 and 64,
+// so the larger tile is the better where the topics fill it.  Rows of kPitch
+// doubles put the four k-steps of a block's reads on different LDS banks.
+// 500 x 500 topics over 100 000 outcomes: 1.2 ms (42 TFLOP/s; a library product
+// of 4 096^2 reaches 61 on this card), 2.28 ms with 64 x 64 tiles, one
+// buffer and no prefetch (22 TFLOP/s).
+template <int TILE>
 __global__ void __launch_bounds__(kThreads) k_bc(const double *__restrict__ P, int32_t kp,
                                                  const double *__restrict__ Q, int32_t kq,
                                                  int64_t V, int64_t slice, int32_t tiles_j,
                                                  double *__restrict__ part)
 {
-    __shared__ double sP[kStage][kTile + kPad], sQ[kStage][kTile + kPad];
-    const int32_t i0 = (int32_t)(blockIdx.x / tiles_j) * kTile;
-    const int32_t j0 = (int32_t)(blockIdx.x % tiles_j) * kTile;
+    constexpr int NB = TILE / 32;                        // blocks per wave and side
+    constexpr int kPitch = TILE + 16;
+    constexpr int kLoads = kStage * TILE / kThreads;     // values of P (and Q) per thread
+    constexpr int kRowStep = kThreads / TILE;
+    __shared__ double sP[2][kStage][kPitch], sQ[2][kStage][kPitch];
+    const int32_t i0 = (int32_t)(blockIdx.x / tiles_j) * TILE;
+    const int32_t j0 = (int32_t)(blockIdx.x % tiles_j) * TILE;
     const int64_t v_beg = (int64_t)blockIdx.y * slice;
     const int64_t v_end = v_beg + slice < V ? v_beg + slice : V;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
+    const int wi = (wave >> 1) * (TILE / 2), wj = (wave & 1) * (TILE / 2);
     // A operand: lane holds row (lane & 15) of the block at k-step (lane >> 4);
     // B operand: column (lane & 15) at k-step (lane >> 4)
     const int kr = lane >> 4, kc = lane & 15;
-    d4 acc00 = {0.0, 0.0, 0.0, 0.0}, acc01 = acc00, acc10 = acc00, acc11 = acc00;
+    // this thread stages column tc of rows tr, tr + kRowStep, ...
+    const int tc = tid % TILE, tr = tid / TILE;
+    const bool in_i = i0 + tc < kp, in_j = j0 + tc < kq;
+    d4 acc[NB][NB];
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
 
-    for (int64_t v0 = v_beg; v0 < v_end; v0 += kStage) {
-        for (int e = tid; e < kStage * kTile; e += kThreads) {
-            const int r = e / kTile, c = e % kTile;
-            const int64_t v = v0 + r;
+    double rp[kLoads], rq[kLoads];
+    auto request = [&](int64_t v0) {
+#pragma unroll
+        for (int e = 0; e < kLoads; ++e) {
+            const int64_t v = v0 + tr + e * kRowStep;
             const bool in_v = v < v_end;
-            sP[r][c] = (in_v && i0 + c < kp) ? sqrt(P[v * kp + i0 + c]) : 0.0;
-            sQ[r][c] = (in_v && j0 + c < kq) ? sqrt(Q[v * kq + j0 + c]) : 0.0;
+            rp[e] = (in_v && in_i) ? P[v * kp + i0 + tc] : 0.0;
+            rq[e] = (in_v && in_j) ? Q[v * kq + j0 + tc] : 0.0;
         }
-        __syncthreads();
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int e = 0; e < kLoads; ++e) {
+            sP[buf][tr + e * kRowStep][tc] = sqrt(rp[e]);
+            sQ[buf][tr + e * kRowStep][tc] = sqrt(rq[e]);
+        }
+    };
+    request(v_beg);
+    stage(0);
+    __syncthreads();
+    int buf = 0;
+    for (int64_t v0 = v_beg; v0 < v_end; v0 += kStage) {
+        const bool more = v0 + kStage < v_end;
+        if (more) request(v0 + kStage);
 #pragma unroll
         for (int ks = 0; ks < kStage; ks += 4) {
-            const double a0 = sP[ks + kr][wi + kc], a1 = sP[ks + kr][wi + 16 + kc];
-            const double b0 = sQ[ks + kr][wj + kc], b1 = sQ[ks + kr][wj + 16 + kc];
-            acc00 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc00, 0, 0, 0);
-            acc01 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc01, 0, 0, 0);
-            acc10 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc10, 0, 0, 0);
-            acc11 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc11, 0, 0, 0);
+            double a[NB], b[NB];
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                a[x] = sP[buf][ks + kr][wi + 16 * x + kc];
+                b[x] = sQ[buf][ks + kr][wj + 16 * x + kc];
+            }
+#pragma unroll
+            for (int x = 0; x < NB; ++x)
+#pragma unroll
+                for (int y = 0; y < NB; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc[x][y], 0, 0, 0);
         }
+        buf ^= 1;
+        if (more) stage(buf);
         __syncthreads();
     }
 
     // result block (fp64 layout): value r of a lane is row 4 r + (lane >> 4),
     // column lane & 15
     double *out = part + (int64_t)blockIdx.y * kp * kq;
-    const d4 acc[2][2] = {{acc00, acc01}, {acc10, acc11}};
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < NB; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+        for (int bj = 0; bj < NB; ++bj)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int32_t i = i0 + wi + bi * 16 + 4 * r + kr;
@@ -136,38 +180,41 @@ int hellinger_scratch(int device, double **out)
     return (int)hipSuccess;
 }
 
+// Tile and outcome slices.  128 x 128 tiles unless they would be filled by less
+// than two thirds of what 64 x 64 tiles are (kp = 65, say), or the outcomes or
+// the partial sums' room allow too few blocks of them for the chip (one block
+// per compute unit at least); with them one slice per two blocks of a compute
+// unit, with 64 x 64 tiles 2 048 blocks, both with at least 16 stages a slice.
 HellingerPlan hellinger_plan(int32_t kp, int32_t kq, int64_t V, int64_t max_part)
 {
-    HellingerPlan p = hellinger_plan(kp, kq, V);
+    HellingerPlan p;
     const int64_t nh = (int64_t)kp * kq;
-    if (nh == 0 || V <= 0) return p;
-    int64_t most = max_part / nh;  // slices whose partial sums fit
-    if (most < 1) most = 1;
-    if (p.slices > most) {
-        const int64_t stages = (V + kStage - 1) / kStage;
-        const int64_t per = (stages + most - 1) / most;
-        p.slice = per * kStage;
-        p.slices = (int32_t)((V + p.slice - 1) / p.slice);
-    }
+    if (nh == 0) return p;  // nothing to launch
+    const int64_t stages = (V + kStage - 1) / kStage;
+    const int64_t room = max_part / nh > 0 ? max_part / nh : 1;  // slices whose sums fit
+    auto tiles_of = [&](int64_t t) { return ((kp + t - 1) / t) * ((kq + t - 1) / t); };
+    auto slices_of = [&](int64_t tiles, int64_t blocks) {
+        int64_t want = (blocks + tiles - 1) / tiles;
+        const int64_t most = (stages + 15) / 16;
+        if (want > most) want = most;
+        if (want > room) want = room;
+        return want < 1 ? (int64_t)1 : want;
+    };
+    const int64_t t64 = tiles_of(kTile), t128 = tiles_of(2 * kTile);
+    const bool large = 8 * t128 <= 3 * t64 && t128 * slices_of(t128, 512) >= 256;
+    p.tile = large ? 2 * kTile : kTile;
+    p.tiles = large ? t128 : t64;
+    p.tiles_j = (kq + p.tile - 1) / p.tile;
+    const int64_t want = slices_of(p.tiles, large ? 512 : 2048);
+    const int64_t per = (stages + want - 1) / want;  // stages per slice
+    p.slice = per * kStage;
+    p.slices = (int32_t)(V > 0 ? (V + p.slice - 1) / p.slice : 1);
     return p;
 }
 
 HellingerPlan hellinger_plan(int32_t kp, int32_t kq, int64_t V)
 {
-    HellingerPlan p;
-    const int64_t tiles = (int64_t)((kp + kTile - 1) / kTile) * ((kq + kTile - 1) / kTile);
-    const int64_t stages = (V + kStage - 1) / kStage;
-    if (tiles == 0) return p;                        // kp or kq = 0: nothing to launch
-    int64_t want = (2048 + tiles - 1) / tiles;      // >= 2048 blocks where V allows
-    const int64_t most = (stages + 15) / 16;         // >= 16 stages per slice
-    if (want > most) want = most;
-    if (want < 1) want = 1;
-    const int64_t per = (stages + want - 1) / want;  // stages per slice
-    p.slice = per * kStage;
-    p.slices = (int32_t)(V > 0 ? (V + p.slice - 1) / p.slice : 1);
-    p.tiles_j = (kq + kTile - 1) / kTile;
-    p.tiles = tiles;
-    return p;
+    return hellinger_plan(kp, kq, V, INT64_MAX);
 }
 
 hipError_t launch_hellinger(const HellingerPlan &p, const double *P, int32_t kp, const double *Q,
@@ -176,8 +223,13 @@ hipError_t launch_hellinger(const HellingerPlan &p, const double *P, int32_t kp,
     const int64_t n = (int64_t)kp * kq;
     if (n == 0) return hipSuccess;
     if (V > 0) {
-        hipLaunchKernelGGL(k_bc, dim3((unsigned)p.tiles, (unsigned)p.slices), dim3(kThreads), 0,
-                           st, P, kp, Q, kq, V, p.slice, p.tiles_j, part);
+        const dim3 grid((unsigned)p.tiles, (unsigned)p.slices);
+        if (p.tile == kTile)
+            hipLaunchKernelGGL(k_bc<kTile>, grid, dim3(kThreads), 0, st, P, kp, Q, kq, V, p.slice,
+                               p.tiles_j, part);
+        else
+            hipLaunchKernelGGL(k_bc<2 * kTile>, grid, dim3(kThreads), 0, st, P, kp, Q, kq, V,
+                               p.slice, p.tiles_j, part);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

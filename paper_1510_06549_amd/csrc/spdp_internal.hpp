@@ -317,7 +317,8 @@ hipError_t launch_foldin(const Model &m, const DeviceBuffers &b, int32_t D_test,
 struct HellingerPlan {
     int64_t slice = 0;   // outcomes per slice (a multiple of the LDS stage)
     int32_t slices = 1;  // outcome slices (grid y)
-    int32_t tiles_j = 1; // 64-wide tiles along kq
+    int32_t tile = 64;   // output tile width, 64 or 128
+    int32_t tiles_j = 1; // tiles along kq
     int64_t tiles = 1;   // output tiles (grid x)
 };
 HellingerPlan hellinger_plan(int32_t kp, int32_t kq, int64_t V);
