@@ -705,7 +705,6 @@ int spdp_estimates(spdp_state *s, int32_t g_begin, int32_t g_end, double *theta,
     if (phi && (g_begin < 0 || g_end > m.G || g_begin > g_end))
         return fail(SPDP_E_ARG, "bad group range");
     HIP_TRY(hipSetDevice(s->device));
-    if (phi) HIP_TRY(widen_rows(s));
     const int64_t vk = (int64_t)m.V * m.K, dk = (int64_t)m.D * m.K;
     // device destinations (the caller's buffers, or one staging buffer reused)
     double *stage = nullptr;
@@ -725,10 +724,15 @@ int spdp_estimates(spdp_state *s, int32_t g_begin, int32_t g_end, double *theta,
         if (e == hipSuccess && where == 0) e = hipStreamSynchronize(s->st);
     };
     out(theta, dk, [&](double *d) { return launch_theta(m, s->b, s->b.zr[s->cur], d, s->st); });
-    out(phi0, vk, [&](double *d) { return launch_phi0(m, s->b, d, s->st); });
-    for (int32_t g = g_begin; phi && g < g_end; ++g)
-        out(phi + (int64_t)(g - g_begin) * vk, vk,
-            [&](double *d) { return launch_phig(m, s->b, g, d, s->st); });
+    if (where == 1) {  // phi0 and every group in one pass
+        if (e == hipSuccess) e = launch_phi(m, s->b, g_begin, g_end, phi0, phi, s->st);
+    } else {
+        out(phi0, vk, [&](double *d) { return launch_phi(m, s->b, 0, 0, d, nullptr, s->st); });
+        for (int32_t g = g_begin; phi && g < g_end; ++g)
+            out(phi + (int64_t)(g - g_begin) * vk, vk, [&](double *d) {
+                return launch_phi(m, s->b, g, g + 1, nullptr, d, s->st);
+            });
+    }
     if (stage) (void)hipFree(stage);
     HIP_TRY(e);
     return sync(s);
@@ -835,7 +839,7 @@ int spdp_hellinger(spdp_state *s, const double *p, int32_t kp, const double *q, 
     double *Hd = h;
     if (!p) {
         double *x = dalloc(np);
-        if (e == hipSuccess) e = launch_phi0(m, s->b, x, s->st);
+        if (e == hipSuccess) e = launch_phi(m, s->b, 0, 0, x, nullptr, s->st);
         Pd = x;
     } else if (!where) {
         Pd = upload(p, np);

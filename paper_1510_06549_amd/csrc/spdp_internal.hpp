@@ -303,9 +303,9 @@ int64_t loglik_partials_needed();
 
 hipError_t launch_theta(const Model &m, const DeviceBuffers &b, const int32_t *zr, double *theta,
                         hipStream_t st);
-hipError_t launch_phi0(const Model &m, const DeviceBuffers &b, double *phi0, hipStream_t st);
-hipError_t launch_phig(const Model &m, const DeviceBuffers &b, int32_t g, double *phi,
-                       hipStream_t st);
+// phi0 [V][K] and phi of groups [g_begin, g_end) [g][V][K] (either may be null)
+hipError_t launch_phi(const Model &m, const DeviceBuffers &b, int32_t g_begin, int32_t g_end,
+                      double *phi0, double *phi, hipStream_t st);
 hipError_t launch_foldin(const Model &m, const DeviceBuffers &b, int32_t D_test,
                          const int32_t *gw, const int64_t *doc_off, const int32_t *doc_group,
                          int32_t n_sweeps, uint64_t seed, int32_t *z, double *ll_doc,
