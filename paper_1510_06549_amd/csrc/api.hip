@@ -168,8 +168,8 @@ hipError_t copy_base16(spdp_state *s)
     return e;
 }
 
-// The sampling step of one sweep, from the sweep-start counts (constants
-// already computed): over weight rows where the state has them.
+// The sampling step of one sweep, from the sweep-start counts and constants:
+// over weight rows where the state has them.
 hipError_t sample_step(spdp_state *s, const int32_t *zr_old, int32_t *zr_new, uint32_t sweep,
                        uint64_t seed)
 {
@@ -558,7 +558,6 @@ int spdp_sweep(spdp_state *s, uint32_t sweep, uint64_t seed)
     DeviceBuffers &b = s->b;
     int32_t *zr_old = b.zr[s->cur], *zr_new = b.zr[1 - s->cur];
     int rc;
-    if ((rc = timed(s, 3, [&] { return launch_factors(m, b, s->st); })) != SPDP_OK) return rc;
     if ((rc = timed(s, 0, [&] { return sample_step(s, zr_old, zr_new, sweep, seed); })) != SPDP_OK)
         return rc;
     // (word associations: source-keyed shadow base)
@@ -1081,7 +1080,6 @@ int spdp_debug_conditionals(spdp_state *s, uint32_t sweep, uint64_t seed, int64_
         HIP_TRY(launch_fill_i32((int32_t *)b.tr_u, T, 0, s->st));
     }
     int32_t *zr_old = b.zr[s->cur], *zr_tmp = b.zr_dbg;
-    HIP_TRY(launch_factors(m, b, s->st));
     if (!trace) {
         HIP_TRY(sample_step(s, zr_old, zr_tmp, sweep, seed));
     } else {

@@ -10,7 +10,8 @@
 //               exclusive scan of the per-row token counts, then a scatter
 //               with one atomic cursor per row; the order inside a row is
 //               free, since nothing below depends on it), built once
-//   k_route     the sampled states copied into row buckets (see below), so
+//   k_route     the rebuild's sums cleared, and the sampled states copied into
+//               row buckets (see below), so
 //               that the rebuild's per-token gathers stay within a region of
 //               the cache's size (the plain model)
 //   k_rows      per row: LDS histogram of its tokens' (z, r) -> the row's
@@ -30,6 +31,7 @@
 //               flag raised when a count does not fit (the samplers then read
 //               B itself, the plain one only where the copy saturates)
 //   k_unpack    export of n and t as separate int32 arrays, [k][w] per group
+#include <algorithm>
 #include <climits>
 
 #include "spdp_internal.hpp"
@@ -46,31 +48,31 @@ inline int64_t blocks_for(int64_t n, int per_block)
     return b < 1 ? 1 : b;
 }
 
-// The row's tokens' states, four per lane in flight: lane l takes row list
-// entries rs + l, rs + l + 64, ... and hands each (token index, state v) to f
-// in any order.  The states are read from their routed copy zr_b, where the
-// states of the rows of one bucket sit together (row_slot: the copy's slot of
-// each row list entry).
-template <typename F>
+// The row's tokens' states, four per lane in flight: lane l of the row's LPR
+// lanes takes row list entries rs + l, rs + l + LPR, ... and hands each (token
+// index, state v) to f in any order.  The states are read from their routed
+// copy zr_b, where the states of the rows of one bucket sit together
+// (row_slot: the copy's slot of each row list entry).
+template <int LPR, typename F>
 __device__ __forceinline__ void for_row_states(int32_t rs, int32_t re, int32_t lane,
                                                const int32_t *__restrict__ perm,
                                                const int32_t *__restrict__ row_slot,
                                                const uint16_t *__restrict__ zr_b, F &&f)
 {
     int32_t j = rs + lane;
-    for (; j + 192 < re; j += 256) {
+    for (; j + 3 * LPR < re; j += 4 * LPR) {
         int32_t t[4], s[4], v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            t[u] = perm[j + 64 * u];
-            s[u] = row_slot[j + 64 * u];
+            t[u] = perm[j + LPR * u];
+            s[u] = row_slot[j + LPR * u];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = (int32_t)zr_b[s[u]];
 #pragma unroll
         for (int u = 0; u < 4; ++u) f(t[u], v[u]);
     }
-    for (; j < re; j += 64) f(perm[j], (int32_t)zr_b[row_slot[j]]);
+    for (; j < re; j += LPR) f(perm[j], (int32_t)zr_b[row_slot[j]]);
 }
 
 // The same, gathering each state from token order (the word-association
@@ -157,10 +159,38 @@ __global__ void k_compose(int64_t N, const int32_t *__restrict__ perm,
     if (j < N) row_slot[j] = tok_slot[perm[j]];
 }
 
-// zr_b[tok_slot[i]] = zr[i] (as 16 bits), four tokens per thread
+// What a rebuild adds into: the shadow-base counts B [nB] and the totals N and
+// T [nT each], zeroed before it (16-byte aligned, lengths multiples of four).
+struct Sums {
+    int32_t *B, *N, *T;
+    int64_t nB, nT;
+};
+
+__device__ __forceinline__ void clear_sums(const Sums &S)
+{
+    const int4 zero = make_int4(0, 0, 0, 0);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < S.nB / 4; i += stride) reinterpret_cast<int4 *>(S.B)[i] = zero;
+    for (int64_t i = first; i < S.nT / 4; i += stride) {
+        reinterpret_cast<int4 *>(S.N)[i] = zero;
+        reinterpret_cast<int4 *>(S.T)[i] = zero;
+    }
+}
+
+// blocks that clear the sums at the memory's rate (a few int4 per thread)
+inline int64_t clear_blocks(const Sums &S)
+{
+    return std::min<int64_t>(blocks_for(std::max(S.nB, S.nT) / 4, kBlock), 2048);
+}
+
+__global__ void __launch_bounds__(kBlock) k_clear_sums(Sums S) { clear_sums(S); }
+
+// zr_b[tok_slot[i]] = zr[i] (as 16 bits), four tokens per thread; the same
+// launch clears the sums of the rebuild (three launches of 3 to 5 us before)
 __global__ void __launch_bounds__(kBlock) k_route(int64_t N, const int32_t *__restrict__ tok_slot,
                                                   const int32_t *__restrict__ zr,
-                                                  uint16_t *__restrict__ zr_b)
+                                                  uint16_t *__restrict__ zr_b, Sums S)
 {
     const int64_t i0 = (int64_t)blockIdx.x * (4 * kBlock) + threadIdx.x;
     int32_t d[4], v[4];
@@ -173,54 +203,69 @@ __global__ void __launch_bounds__(kBlock) k_route(int64_t N, const int32_t *__re
 #pragma unroll
     for (int u = 0; u < 4; ++u)
         if (d[u] >= 0) zr_b[d[u]] = (uint16_t)v[u];
+    clear_sums(S);
 }
 
-// One 64-lane block per count row; the row's histogram and the smallest token
-// index of each topic in LDS (2 Kp ints of dynamic shared memory).  Every
-// token's state is read once: a cell left with customers but no table holds
-// only r = 0 tokens, and its smallest-index token becomes its head.  Blocks
-// are dealt to the 8 XCDs in turn; block b rebuilds row
-// (b mod 8) rows_per_xcd + b / 8, so that each XCD walks its own run of rows
-// in order and the bucket of routed states its rows gather from stays in that
-// XCD's L2 (blocks past the last row return).
-__global__ void __launch_bounds__(64) k_rows(int64_t rows, int64_t rows_per_xcd, int32_t V,
-                                             int32_t Kp,
-                                             const int32_t *__restrict__ row_off,
-                                             const int32_t *__restrict__ perm,
-                                             const int32_t *__restrict__ row_slot,
-                                             const uint16_t *__restrict__ zr_b,
-                                             const uint8_t *__restrict__ row_narrow,
-                                             int32_t *__restrict__ zr, int32_t *__restrict__ nt,
-                                             uint16_t *__restrict__ nt16, int32_t *__restrict__ B,
-                                             uint32_t *__restrict__ rep_part)
+// LPR lanes per count row (64, or 32 for rows of at most 128 cells, whose rows
+// are mostly short), 64 / LPR rows per wavefront and WAVES wavefronts a block;
+// the row's histogram and the smallest token index of each topic in LDS (2 Kp
+// ints of dynamic shared memory per row).  Every token's state is read once: a
+// cell left with customers but no table holds only r = 0 tokens, and its
+// smallest-index token becomes its head.  A row is one wavefront's own, so its
+// phases need no barrier, only the order of that wavefront's LDS operations.
+// Blocks are dealt to the 8 XCDs in turn; block b rebuilds the rows from
+// (b mod 8) rows_per_xcd + (b / 8) rows-per-block on, so that each XCD walks
+// its own run of rows in order and the bucket of routed states its rows gather
+// from stays in that XCD's L2.  One row per 64-lane block took 136 us for 468 000
+// rows of 32 topics (3 M tokens) and 14 us for 29 000 rows of 64, most of it
+// launching and filling wavefronts for a few tokens each.
+template <int LPR, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) k_rows(int64_t rows, int64_t rows_per_xcd, int32_t V,
+                                                     int32_t Kp,
+                                                     const int32_t *__restrict__ row_off,
+                                                     const int32_t *__restrict__ perm,
+                                                     const int32_t *__restrict__ row_slot,
+                                                     const uint16_t *__restrict__ zr_b,
+                                                     const uint8_t *__restrict__ row_narrow,
+                                                     int32_t *__restrict__ zr,
+                                                     int32_t *__restrict__ nt,
+                                                     uint16_t *__restrict__ nt16,
+                                                     int32_t *__restrict__ B,
+                                                     uint32_t *__restrict__ rep_part)
 {
+    constexpr int RPB = WAVES * 64 / LPR;
     extern __shared__ int32_t rows_lds[];
-    int32_t *h = rows_lds, *first = rows_lds + Kp;
-    const int64_t q = (int64_t)(blockIdx.x & 7) * rows_per_xcd + (blockIdx.x >> 3);
-    if (q >= rows) return;
-    const int32_t lane = threadIdx.x;
-    const int32_t rs = row_off[q], re = row_off[q + 1];
+    const int32_t lane = threadIdx.x % LPR, slot = threadIdx.x / LPR;
+    int32_t *h = rows_lds + slot * 2 * Kp, *first = h + Kp;
+    const int64_t local = (int64_t)(blockIdx.x >> 3) * RPB + slot;
+    const int64_t q = (int64_t)(blockIdx.x & 7) * rows_per_xcd + local;
+    const bool mine = local < rows_per_xcd && q < rows;
+    const int32_t rs = mine ? row_off[q] : 0, re = mine ? row_off[q + 1] : 0;
     uint32_t rep = 0;
     if (rs < re) {
-        for (int32_t k = lane; k < Kp; k += 64) {
+        for (int32_t k = lane; k < Kp; k += LPR) {
             h[k] = 0;
             first[k] = INT_MAX;
         }
-        __syncthreads();
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (rs < re) {
         // the gathers at wave priority 2, so that a row's loads leave ahead of
         // the other wavefronts' row writes
         __builtin_amdgcn_s_setprio(2);
-        for_row_states(rs, re, lane, perm, row_slot, zr_b, [&](int32_t tok, int32_t v) {
+        for_row_states<LPR>(rs, re, lane, perm, row_slot, zr_b, [&](int32_t tok, int32_t v) {
             atomicAdd(&h[v >> 1], 1 + ((v & 1) << 16));
             atomicMin(&first[v >> 1], tok);
         });
         __builtin_amdgcn_s_setprio(0);
-        __syncthreads();
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (rs < re) {
         int32_t *__restrict__ row = nt + q * Kp;
         uint16_t *__restrict__ row16 = nt16 + q * Kp;
         int32_t *__restrict__ base = B + (q % V) * Kp;
         const bool nar = row_narrow[q] != 0;
-        for (int32_t k = lane; k < Kp; k += 64) {
+        for (int32_t k = lane; k < Kp; k += LPR) {
             int32_t x = h[k];
             if (x != 0 && (x >> 16) == 0) {
                 const int32_t tok = first[k];
@@ -233,8 +278,8 @@ __global__ void __launch_bounds__(64) k_rows(int64_t rows, int64_t rows_per_xcd,
             if (x >> 16) atomicAdd(&base[k], x >> 16);
         }
     }
-    for (int o = 32; o > 0; o >>= 1) rep += __shfl_xor(rep, o);
-    if (lane == 0) rep_part[q] = rep;
+    for (int o = LPR / 2; o > 0; o >>= 1) rep += __shfl_xor(rep, o);
+    if (mine && lane == 0) rep_part[q] = rep;
 }
 
 // Word associations: the same per-row rebuild, where a promoted head takes
@@ -709,16 +754,21 @@ hipError_t build_visit_order(const Model &m, DeviceBuffers &b, hipStream_t st)
 hipError_t launch_rows(const Model &m, const DeviceBuffers &b, int32_t *zr, hipStream_t st)
 {
     const int64_t rows = (int64_t)m.G * m.V;
-    hipError_t e = launch_fill_i32(b.B, (int64_t)m.V * m.Kp, 0, st);
-    if (e != hipSuccess) return e;
-    if (m.N > 0)
-        hipLaunchKernelGGL(k_route, dim3((unsigned)blocks_for(m.N, 4 * kBlock)), dim3(kBlock), 0, st,
-                           m.N, b.tok_slot, zr, b.zr_b);
-    const size_t lds = 2 * (size_t)m.Kp * sizeof(int32_t);
+    const Sums S{b.B, b.Ngk, b.Tgk, (int64_t)m.V * m.Kp, (int64_t)m.G * m.Kp};
+    hipLaunchKernelGGL(k_route, dim3((unsigned)std::max(blocks_for(m.N, 4 * kBlock), clear_blocks(S))),
+                       dim3(kBlock), 0, st, m.N, b.tok_slot, zr, b.zr_b, S);
     const int64_t rows_per_xcd = (rows + 7) / 8;
-    hipLaunchKernelGGL(k_rows, dim3((unsigned)(8 * rows_per_xcd)), dim3(64), lds, st, rows,
-                       rows_per_xcd, m.V, m.Kp, b.row_off, b.perm, b.row_slot, b.zr_b,
-                       b.row_narrow, zr, b.nt, b.nt16, b.B, b.rep_part);
+    const size_t row_lds = 2 * (size_t)m.Kp * sizeof(int32_t);
+    if (m.Kp <= 128) {  // 8 rows a block
+        const unsigned nb = (unsigned)((rows_per_xcd + 7) / 8);
+        hipLaunchKernelGGL((k_rows<32, 4>), dim3(8 * nb), dim3(256), 8 * row_lds, st, rows,
+                           rows_per_xcd, m.V, m.Kp, b.row_off, b.perm, b.row_slot, b.zr_b,
+                           b.row_narrow, zr, b.nt, b.nt16, b.B, b.rep_part);
+    } else {
+        hipLaunchKernelGGL((k_rows<64, 1>), dim3((unsigned)(8 * rows_per_xcd)), dim3(64), row_lds,
+                           st, rows, rows_per_xcd, m.V, m.Kp, b.row_off, b.perm, b.row_slot,
+                           b.zr_b, b.row_narrow, zr, b.nt, b.nt16, b.B, b.rep_part);
+    }
     return hipGetLastError();
 }
 
@@ -733,8 +783,8 @@ hipError_t launch_widen(const Model &m, const DeviceBuffers &b, hipStream_t st)
 hipError_t launch_rows_assoc(const Model &m, const DeviceBuffers &b, int32_t *zr, hipStream_t st)
 {
     const int64_t rows = (int64_t)m.G * m.V;
-    hipError_t e = launch_fill_i32(b.B, (int64_t)m.V * m.Kp, 0, st);
-    if (e != hipSuccess) return e;
+    const Sums S{b.B, b.Ngk, b.Tgk, (int64_t)m.V * m.Kp, (int64_t)m.G * m.Kp};
+    hipLaunchKernelGGL(k_clear_sums, dim3((unsigned)clear_blocks(S)), dim3(kBlock), 0, st, S);
     const size_t lds = 2 * (size_t)m.Kp * sizeof(int32_t);
     hipLaunchKernelGGL(k_rows_assoc, dim3((unsigned)rows), dim3(64), lds, st, m.Kp, m.Sp,
                        b.row_off, b.perm, b.srcrec, b.head_slot, b.row_narrow, zr, b.nt, b.nt16,

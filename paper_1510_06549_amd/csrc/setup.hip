@@ -306,38 +306,67 @@ __global__ void k_topic_tables(int32_t G, int32_t Kp, const int32_t *__restrict_
 //   fk[2] = (b + a (T - 1)) / (b + N - 1) / (V gamma + B_k - 1)  (r = 1 removed)
 // Padding topics (k >= K) get 0, so their outcomes carry zero weight.  fz (may
 // be null) holds the same five per topic: {fk[0], fk[1], fk[2], 0}, {f0, f1, 0, 0}.
-__global__ void k_factors(int32_t G, int32_t K, int32_t Kp, double a, double b, double Vgamma,
-                          const int32_t *__restrict__ Ngk, const int32_t *__restrict__ Tgk,
-                          const int32_t *__restrict__ Bk, float *__restrict__ f0,
-                          float *__restrict__ f1, float *__restrict__ fk,
-                          float4 *__restrict__ fz)
+struct FactorArgs {
+    const int32_t *Ngk, *Tgk;
+    float *f0, *f1, *fk;
+    float4 *fz;
+    int64_t GK;
+    int32_t K;
+    double a, b, Vgamma;
+};
+
+__device__ __forceinline__ void factors_of(const FactorArgs &A, int64_t j, int32_t k, int32_t Bk)
 {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t GK = (int64_t)G * Kp;
-    if (j >= GK) return;
-    const int32_t k = (int32_t)(j % Kp);
     float c0 = 0.0f, c1 = 0.0f, d0 = 0.0f, d1 = 0.0f, d2 = 0.0f;
-    if (k < K) {
-        const double N = (double)Ngk[j], T = (double)Tgk[j], B = (double)Bk[k];
-        const double inv = 1.0 / (b + N);
+    if (k < A.K) {
+        const double N = (double)A.Ngk[j], T = (double)A.Tgk[j], B = (double)Bk;
+        const double inv = 1.0 / (A.b + N);
         c0 = (float)inv;
-        c1 = (float)((b + a * T) * inv / (Vgamma + B));
-        if (Ngk[j] >= 1) {
-            const double invm = 1.0 / (b + N - 1.0);
+        c1 = (float)((A.b + A.a * T) * inv / (A.Vgamma + B));
+        if (A.Ngk[j] >= 1) {
+            const double invm = 1.0 / (A.b + N - 1.0);
             d0 = (float)invm;
-            d1 = (float)((b + a * T) * invm / (Vgamma + B));
-            if (Tgk[j] >= 1) d2 = (float)((b + a * (T - 1.0)) * invm / (Vgamma + B - 1.0));
+            d1 = (float)((A.b + A.a * T) * invm / (A.Vgamma + B));
+            if (A.Tgk[j] >= 1)
+                d2 = (float)((A.b + A.a * (T - 1.0)) * invm / (A.Vgamma + B - 1.0));
         }
     }
-    f0[j] = c0;
-    f1[j] = c1;
-    fk[j] = d0;
-    fk[GK + j] = d1;
-    fk[2 * GK + j] = d2;
-    if (fz) {
-        fz[2 * j] = make_float4(d0, d1, d2, 0.0f);
-        fz[2 * j + 1] = make_float4(c0, c1, 0.0f, 0.0f);
+    A.f0[j] = c0;
+    A.f1[j] = c1;
+    A.fk[j] = d0;
+    A.fk[A.GK + j] = d1;
+    A.fk[2 * A.GK + j] = d2;
+    if (A.fz) {
+        A.fz[2 * j] = make_float4(d0, d1, d2, 0.0f);
+        A.fz[2 * j + 1] = make_float4(c0, c1, 0.0f, 0.0f);
     }
+}
+
+__global__ void k_factors(FactorArgs A, int32_t Kp, const int32_t *__restrict__ Bk)
+{
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < A.GK) factors_of(A, j, (int32_t)(j % Kp), Bk[j % Kp]);
+}
+
+// B_k and the constants in one launch, for few groups: a block takes
+// kTabTopics topics, kTabRows threads each, which share the groups of a topic.
+constexpr int kTabTopics = 8, kTabRows = 32;
+__global__ void __launch_bounds__(kTabTopics *kTabRows) k_tables_factors(FactorArgs A, int32_t G,
+                                                                         int32_t Kp,
+                                                                         int32_t *__restrict__ Bk)
+{
+    __shared__ int32_t part[kTabRows][kTabTopics];
+    const int32_t x = threadIdx.x % kTabTopics, y = threadIdx.x / kTabTopics;
+    const int32_t k = blockIdx.x * kTabTopics + x;  // (Kp is a multiple of kTabTopics)
+    int32_t s = 0;
+    for (int32_t g = y; g < G; g += kTabRows) s += A.Tgk[(int64_t)g * Kp + k];
+    part[y][x] = s;
+    __syncthreads();
+    int32_t B = 0;
+#pragma unroll
+    for (int i = 0; i < kTabRows; ++i) B += part[i][x];
+    if (y == 0) Bk[k] = B;
+    for (int32_t g = y; g < G; g += kTabRows) factors_of(A, (int64_t)g * Kp + k, k, B);
 }
 
 }  // namespace
@@ -430,9 +459,46 @@ hipError_t launch_unpack_zr(const Model &m, const int32_t *zr, int32_t *z, uint8
     return hipGetLastError();
 }
 
+// N_gk and T_gk of the states into arrays that are zero
+static hipError_t add_totals(const Model &m, const DeviceBuffers &b, const int32_t *zr,
+                             int32_t *Ngk, int32_t *Tgk, hipStream_t st)
+{
+    if (m.N <= 0) return hipSuccess;
+    const int64_t bins = (int64_t)m.G * m.Kp;
+    // (if the queries fail, lds_max stays 0 and the global-atomic histogram runs)
+    int dev = 0, lds_max = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    const int64_t lds = bins * (int64_t)sizeof(uint32_t);
+    if (lds <= lds_max && lds <= 96 * 1024) {
+        const unsigned nb = (unsigned)blocks_for(m.N, kTotalsChunk);
+        hipLaunchKernelGGL(k_totals_lds, dim3(nb), dim3(1024), (size_t)lds, st, m.N, m.Kp,
+                           (int32_t)bins, m.divV, b.gw, zr, Ngk, Tgk);
+    } else {
+        hipLaunchKernelGGL(k_totals_global, dim3((unsigned)blocks_for(m.N, kBlock)), dim3(kBlock),
+                           0, st, m.N, m.Kp, m.divV, b.gw, zr, Ngk, Tgk);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_totals(const Model &m, const DeviceBuffers &b, const int32_t *zr, hipStream_t st)
 {
-    return launch_totals_into(m, b, zr, b.Ngk, b.Tgk, b.Bk, st);
+    hipError_t e = add_totals(m, b, zr, b.Ngk, b.Tgk, st);
+    if (e != hipSuccess) return e;
+    const int64_t GK = (int64_t)m.G * m.Kp;
+    const FactorArgs A{b.Ngk, b.Tgk, b.f0, b.f1, b.fk, b.fz, GK,
+                       m.K,   m.a,   m.b,  (double)m.V * m.gamma};
+    // one launch where each thread has at most two groups of its topic
+    if (m.G <= 2 * kTabRows) {
+        hipLaunchKernelGGL(k_tables_factors, dim3((unsigned)(m.Kp / kTabTopics)),
+                           dim3(kTabTopics * kTabRows), 0, st, A, m.G, m.Kp, b.Bk);
+    } else {
+        hipLaunchKernelGGL(k_topic_tables, dim3((unsigned)blocks_for(m.Kp, kBlock)), dim3(kBlock),
+                           0, st, m.G, m.Kp, b.Tgk, b.Bk);
+        hipLaunchKernelGGL(k_factors, dim3((unsigned)blocks_for(GK, kBlock)), dim3(kBlock), 0, st,
+                           A, m.Kp, b.Bk);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_totals_into(const Model &m, const DeviceBuffers &b, const int32_t *zr,
@@ -442,22 +508,7 @@ hipError_t launch_totals_into(const Model &m, const DeviceBuffers &b, const int3
     const int64_t bins = (int64_t)m.G * m.Kp;
     if ((e = fill(Ngk, bins, 0, st)) != hipSuccess) return e;
     if ((e = fill(Tgk, bins, 0, st)) != hipSuccess) return e;
-    if (m.N > 0) {
-        // (if the queries fail, lds_max stays 0 and the global-atomic histogram runs)
-        int dev = 0, lds_max = 0;
-        (void)hipGetDevice(&dev);
-        (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-        const int64_t lds = bins * (int64_t)sizeof(uint32_t);
-        if (lds <= lds_max && lds <= 96 * 1024) {
-            const unsigned nb = (unsigned)blocks_for(m.N, kTotalsChunk);
-            hipLaunchKernelGGL(k_totals_lds, dim3(nb), dim3(1024), (size_t)lds, st, m.N, m.Kp,
-                               (int32_t)bins, m.divV, b.gw, zr, Ngk, Tgk);
-        } else {
-            hipLaunchKernelGGL(k_totals_global, dim3((unsigned)blocks_for(m.N, kBlock)), dim3(kBlock),
-                               0, st, m.N, m.Kp, m.divV, b.gw, zr, Ngk, Tgk);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    if ((e = add_totals(m, b, zr, Ngk, Tgk, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_topic_tables, dim3((unsigned)blocks_for(m.Kp, kBlock)), dim3(kBlock), 0, st,
                        m.G, m.Kp, Tgk, Bk);
     return hipGetLastError();
@@ -473,15 +524,6 @@ hipError_t launch_narrow_flags(const Model &m, const int32_t *gw, const int32_t 
     if (m.N > 0)
         hipLaunchKernelGGL(k_tok_narrow, dim3((unsigned)blocks_for(m.N, kBlock)), dim3(kBlock), 0,
                            st, m.N, gw, row_narrow, tok_narrow);
-    return hipGetLastError();
-}
-
-hipError_t launch_factors(const Model &m, const DeviceBuffers &b, hipStream_t st)
-{
-    const int64_t n = (int64_t)m.G * m.Kp;
-    hipLaunchKernelGGL(k_factors, dim3((unsigned)blocks_for(n, kBlock)), dim3(kBlock), 0, st, m.G,
-                       m.K, m.Kp, m.a, m.b, (double)m.V * m.gamma, b.Ngk, b.Tgk, b.Bk, b.f0, b.f1,
-                       b.fk, b.fz);
     return hipGetLastError();
 }
 

@@ -239,14 +239,15 @@ hipError_t launch_unpack_zr(const Model &m, const int32_t *zr, int32_t *z, uint8
 hipError_t build_row_index(const Model &m, DeviceBuffers &b, const int32_t *gw_count,
                            hipStream_t st);
 // count rows with the repair, and the shadow-base counts B (zeroed, then each
-// row's table counts added) of the plain model, from the state zr
+// row's table counts added) of the plain model, from the state zr; the totals
+// N_gk and T_gk are zeroed too
 hipError_t launch_rows(const Model &m, const DeviceBuffers &b, int32_t *zr, hipStream_t st);
 // the 32-bit rows of the narrow rows from their 16-bit copies (the rebuild
 // writes a narrow row only as its copy; entry points that read 32-bit rows
 // call this first)
 hipError_t launch_widen(const Model &m, const DeviceBuffers &b, hipStream_t st);
 // word associations: count rows with the repair, and the shadow-base counts
-// keyed by source (B zeroed, then one increment per head)
+// keyed by source (B zeroed, then one increment per head); N_gk and T_gk zeroed
 hipError_t launch_rows_assoc(const Model &m, const DeviceBuffers &b, int32_t *zr, hipStream_t st);
 // B16 and the width flag from B (after either rebuild)
 hipError_t launch_base16(const Model &m, const DeviceBuffers &b, hipStream_t st);
@@ -264,12 +265,13 @@ hipError_t launch_check(const Model &m, const DeviceBuffers &b, const int32_t *z
 hipError_t launch_stat_sums(const Model &m, const DeviceBuffers &b, const int32_t *zr_now,
                             const int32_t *zr_before, hipStream_t st);
 int64_t stat_partials_needed();
+// N_gk and T_gk of the states (into the arrays that the row rebuild cleared),
+// B_k, and the per-sweep constants of the samplers
 hipError_t launch_totals(const Model &m, const DeviceBuffers &b, const int32_t *zr,
                          hipStream_t st);
-// the same into other arrays (N, T: [G][Kp], Bk: [Kp])
+// the totals alone, into other arrays (N, T: [G][Kp], Bk: [Kp])
 hipError_t launch_totals_into(const Model &m, const DeviceBuffers &b, const int32_t *zr,
                               int32_t *Ngk, int32_t *Tgk, int32_t *Bk, hipStream_t st);
-hipError_t launch_factors(const Model &m, const DeviceBuffers &b, hipStream_t st);
 hipError_t launch_sample(const Model &m, const DeviceBuffers &b, const int32_t *zr_old,
                          int32_t *zr_new, uint32_t sweep, uint64_t seed, float *tr_w,
                          float *tr_u, int64_t tr_begin, int64_t tr_end, hipStream_t st);
