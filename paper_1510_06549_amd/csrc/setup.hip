@@ -244,12 +244,22 @@ __global__ void k_unpack_zr(int64_t N, const int32_t *__restrict__ zr, int32_t *
 }
 
 // ----------------------------------------------------------------- totals
-// Per block, a chunk of at most 65535 tokens is histogrammed into LDS bins of
+// Per block, a chunk of at most 32768 tokens is histogrammed into LDS bins of
 // (g, k), each bin packing customers (low 16 bits) and tables (high 16 bits);
-// non-zero bins are flushed with global atomics.
-constexpr int kTotalsChunk = 32768;
+// non-zero bins are flushed with global atomics.  Chunks are shorter where
+// there would be fewer blocks than compute units (500 000 tokens: 13 us
+// in 16 blocks, 4.6 us in 244), down to a few tokens per thread.
+constexpr int kTotalsChunk = 32768, kTotalsLeast = 2048;
 
-__global__ void __launch_bounds__(1024) k_totals_lds(int64_t N, int32_t Kp, int32_t bins,
+inline int32_t totals_chunk(int64_t N)
+{
+    int32_t c = kTotalsChunk;
+    while (c > kTotalsLeast && N / c < 256) c /= 2;
+    return c;
+}
+
+__global__ void __launch_bounds__(1024) k_totals_lds(int64_t N, int32_t chunk, int32_t Kp,
+                                                     int32_t bins,
                                                      FastDiv divV, const int32_t *__restrict__ gw,
                                                      const int32_t *__restrict__ zr,
                                                      int32_t *__restrict__ Ngk,
@@ -258,8 +268,8 @@ __global__ void __launch_bounds__(1024) k_totals_lds(int64_t N, int32_t Kp, int3
     extern __shared__ uint32_t h[];
     for (int j = threadIdx.x; j < bins; j += blockDim.x) h[j] = 0u;
     __syncthreads();
-    const int64_t beg = (int64_t)blockIdx.x * kTotalsChunk;
-    const int64_t end = min(beg + (int64_t)kTotalsChunk, N);
+    const int64_t beg = (int64_t)blockIdx.x * chunk;
+    const int64_t end = min(beg + (int64_t)chunk, N);
     for (int64_t i = beg + threadIdx.x; i < end; i += blockDim.x) {
         const int32_t v = zr[i];
         const int32_t g = (int32_t)fastdiv((uint32_t)gw[i], divV);
@@ -471,8 +481,9 @@ static hipError_t add_totals(const Model &m, const DeviceBuffers &b, const int32
     (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     const int64_t lds = bins * (int64_t)sizeof(uint32_t);
     if (lds <= lds_max && lds <= 96 * 1024) {
-        const unsigned nb = (unsigned)blocks_for(m.N, kTotalsChunk);
-        hipLaunchKernelGGL(k_totals_lds, dim3(nb), dim3(1024), (size_t)lds, st, m.N, m.Kp,
+        const int32_t chunk = totals_chunk(m.N);
+        const unsigned nb = (unsigned)blocks_for(m.N, chunk);
+        hipLaunchKernelGGL(k_totals_lds, dim3(nb), dim3(1024), (size_t)lds, st, m.N, chunk, m.Kp,
                            (int32_t)bins, m.divV, b.gw, zr, Ngk, Tgk);
     } else {
         hipLaunchKernelGGL(k_totals_global, dim3((unsigned)blocks_for(m.N, kBlock)), dim3(kBlock),
