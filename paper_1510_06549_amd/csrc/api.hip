@@ -86,6 +86,38 @@ int dev_alloc(spdp_state *s, T **p, int64_t count, const char *what)
     return SPDP_OK;
 }
 
+// Device arrays of a state that are allocated together: one hipMalloc for all
+// of them (each call, and each hipFree when the state goes, costs 30 to 60 us,
+// and a state has some forty arrays), every array on a 256-byte boundary.
+class Arrays {
+public:
+    template <typename T>
+    void add(T **p, int64_t count)
+    {
+        *p = nullptr;
+        if (count <= 0) count = 1;
+        parts_[n_++] = {reinterpret_cast<void **>(p), total_};
+        total_ += ((size_t)count * sizeof(T) + 255) / 256 * 256;
+    }
+    int alloc(spdp_state *s, const char *what)
+    {
+        char *base = nullptr;
+        const int rc = dev_alloc(s, &base, (int64_t)total_, what);
+        if (rc != SPDP_OK) return rc;
+        for (int i = 0; i < n_; ++i) *parts_[i].p = base + parts_[i].at;
+        return SPDP_OK;
+    }
+
+private:
+    struct Part {
+        void **p;
+        size_t at;
+    };
+    Part parts_[24] = {};  // the largest list has 22 arrays
+    int n_ = 0;
+    size_t total_ = 0;
+};
+
 void free_state(spdp_state *s)
 {
     if (!s) return;
@@ -375,35 +407,36 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
     DeviceBuffers &B = s->b;
     const int64_t rows = (int64_t)G * V;
 
-    // corpus
-    int32_t *words_d = nullptr, *gw_count = nullptr;
-    TRY(dev_alloc(s, &B.gw, N, "token rows"));
-    TRY(dev_alloc(s, &B.doc_off, (int64_t)D + 1, "doc offsets"));
-    TRY(dev_alloc(s, &B.doc_group, D, "doc groups"));
-    TRY(dev_alloc(s, &B.err, 2, "error flags"));
-    TRY(dev_alloc(s, &B.ctr, 4, "counters"));
-    TRY(dev_alloc(s, &B.claim, 9, "document claims"));
-    TRY_HIP(launch_fill_i32(B.claim, 9, 0, s->st));
-    TRY(dev_alloc(s, &B.scalar, 1, "scalar"));
-    TRY_HIP(launch_fill_i32(B.err, 2, 0, s->st));
+    // corpus, states and row index; the words are staged in the second state
+    // buffer and the per-row token counts in the repair partials
+    int32_t *scan_tmp = nullptr;
     {
-        void *tmp = nullptr;
-        if (hipMalloc(&tmp, (size_t)(N > 0 ? N : 1) * sizeof(int32_t)) != hipSuccess) {
-            (void)hipGetLastError();
-            TRY(fail(SPDP_E_NOMEM, "staging buffer for words"));
+        Arrays a;
+        a.add(&B.gw, N);
+        a.add(&B.doc_off, (int64_t)D + 1);
+        a.add(&B.doc_group, D);
+        a.add(&B.err, 2);
+        a.add(&B.ctr, 4);
+        a.add(&B.claim, 9);
+        a.add(&B.scalar, 2);
+        a.add(&B.perm, N);
+        a.add(&B.row_off, rows + 1);
+        a.add(&B.row_narrow, rows);
+        a.add(&B.tok_narrow, N);
+        a.add(&B.zr[0], N);
+        a.add(&B.zr[1], N);
+        a.add(&B.rep_part, rows + 1);
+        a.add(&scan_tmp, row_index_scratch(N, rows));
+        if (!assoc) {  // the plain model's rebuild gathers from routed states
+            a.add(&B.tok_slot, N);
+            a.add(&B.row_slot, N);
+            a.add(&B.zr_b, N);
         }
-        words_d = (int32_t *)tmp;
-        if (hipMalloc(&tmp, (size_t)(rows + 1) * sizeof(int32_t)) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipFree(words_d);
-            TRY(fail(SPDP_E_NOMEM, "staging buffer for word counts"));
-        }
-        gw_count = (int32_t *)tmp;
+        TRY(a.alloc(s, "the corpus and its row index"));
     }
-    auto cleanup_staging = [&]() {
-        (void)hipFree(words_d);
-        (void)hipFree(gw_count);
-    };
+    int32_t *words_d = B.zr[1], *gw_count = reinterpret_cast<int32_t *>(B.rep_part);
+    TRY_HIP(launch_fill_i32(B.claim, 9, 0, s->st));
+    TRY_HIP(launch_fill_i32(B.err, 2, 0, s->st));
     hipError_t e = hipSuccess;
     if (N > 0)
         e = hipMemcpyAsync(words_d, corpus->words, (size_t)N * sizeof(int32_t),
@@ -420,9 +453,7 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
     int32_t herr[2] = {0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(herr, B.err, sizeof herr, hipMemcpyDeviceToHost, s->st);
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);
-    if (e != hipSuccess) cleanup_staging();
     TRY_HIP(e);
-    if ((herr[0] & 3) || herr[1] > kCountMax) cleanup_staging();
     if (herr[0] & 1) TRY(fail(SPDP_E_ARG, "doc_group out of [0, n_groups)"));
     if (herr[0] & 2) TRY(fail(SPDP_E_ARG, "word id out of [0, vocab)"));
     if (herr[1] > kCountMax)
@@ -435,28 +466,11 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
     // whose (group, word) pair occurs at most kNarrowMax times (fixed by the
     // corpus) also get 16-bit copies
     unsigned long long n_rows[2] = {0, 0};  // narrow rows, rows that have tokens
-    {
-        int rc2 = dev_alloc(s, &B.perm, N, "row-sorted tokens");
-        if (!assoc) {  // the plain model's rebuild gathers from routed states
-            if (rc2 == SPDP_OK) rc2 = dev_alloc(s, &B.tok_slot, N, "state route of tokens");
-            if (rc2 == SPDP_OK) rc2 = dev_alloc(s, &B.row_slot, N, "state route of row entries");
-            if (rc2 == SPDP_OK) rc2 = dev_alloc(s, &B.zr_b, N, "routed states");
-        }
-        if (rc2 == SPDP_OK) rc2 = dev_alloc(s, &B.row_off, rows + 1, "row offsets");
-        if (rc2 == SPDP_OK) rc2 = dev_alloc(s, &B.row_narrow, rows, "narrow-row flags");
-        if (rc2 == SPDP_OK) rc2 = dev_alloc(s, &B.tok_narrow, N, "narrow-row flags of tokens");
-        if (rc2 != SPDP_OK) cleanup_staging();
-        TRY(rc2);
-        e = build_row_index(m, B, gw_count, s->st);
-        if (e == hipSuccess) e = launch_fill_u64(B.ctr, 4, 0, s->st);
-        if (e == hipSuccess)
-            e = launch_narrow_flags(m, B.gw, gw_count, B.row_narrow, B.tok_narrow, B.ctr, s->st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(n_rows, B.ctr, sizeof n_rows, hipMemcpyDeviceToHost, s->st);
-        if (e == hipSuccess) e = hipStreamSynchronize(s->st);
-        cleanup_staging();
-        TRY_HIP(e);
-    }
+    TRY_HIP(launch_fill_u64(B.ctr, 4, 0, s->st));
+    TRY_HIP(launch_narrow_flags(m, B.gw, gw_count, B.row_narrow, B.tok_narrow, B.ctr, s->st));
+    TRY_HIP(hipMemcpyAsync(n_rows, B.ctr, sizeof n_rows, hipMemcpyDeviceToHost, s->st));
+    TRY_HIP(build_row_index(m, B, gw_count, scan_tmp, s->st));
+    TRY_HIP(hipStreamSynchronize(s->st));
     s->n_narrow_rows = (int64_t)n_rows[0];
 
     // word associations
@@ -469,45 +483,47 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         TRY(fail(SPDP_E_RANGE,
                  "a (group, word) pair occurs %d times; the Stirling cache covers at most %d",
                  m.ncap, kMaxNcap));
-    TRY(dev_alloc(s, &B.logS, n_logS, "log Stirling table"));
-    TRY(dev_alloc(s, &B.Q, n_Q, "Stirling ratio pairs"));
-    TRY(dev_alloc(s, &B.Q64, n_Q, "fp64 Stirling ratio pairs"));
-    TRY(dev_alloc(s, &B.lfact, (int64_t)m.ncap + 1, "log factorials"));
-    TRY_HIP(launch_stirling(m, B.logS, B.Q, B.Q64, B.lfact, s->st));
-
-    // state and counts
-    TRY(dev_alloc(s, &B.zr[0], N, "zr"));
-    TRY(dev_alloc(s, &B.zr[1], N, "zr"));
-    TRY(dev_alloc(s, &B.nt, rows * m.Kp, "packed customer/table counts"));
-    TRY(dev_alloc(s, &B.B, (int64_t)V * m.Kp, "shadow-base table counts"));
-    TRY(dev_alloc(s, &B.B16, (int64_t)V * m.Kp, "16-bit shadow-base table counts"));
-    TRY(dev_alloc(s, &B.wide, 1, "shadow-base width flag"));
-    TRY_HIP(launch_fill_i32(B.nt, rows * m.Kp, 0, s->st));
+    m.rows = row_shape(N, D, rows, (int64_t)n_rows[1], K);
     // (the 16-bit copies: a buffer of the full row count, so that row q's copy
     // sits at q Kp; only the narrow rows' copies are written and read; the
     // sampler's vector reads of a narrow row run at most 4 cells past its
     // end, which the 64-cell tail keeps inside the buffer)
     const int64_t n16 = (n_rows[0] > 0 ? rows * m.Kp : 0) + 64;
-    TRY(dev_alloc(s, &B.nt16, n16, "narrow count rows"));
-    TRY_HIP(launch_fill_i32(reinterpret_cast<int32_t *>(B.nt16), n16 / 2, 0, s->st));
-    TRY(dev_alloc(s, &B.Ngk, (int64_t)G * m.Kp, "N_gk"));
-    TRY(dev_alloc(s, &B.Tgk, (int64_t)G * m.Kp, "T_gk"));
-    TRY(dev_alloc(s, &B.Bk, m.Kp, "B_k"));
-    TRY(dev_alloc(s, &B.f0, (int64_t)G * m.Kp, "f0"));
-    TRY(dev_alloc(s, &B.f1, (int64_t)G * m.Kp, "f1"));
-    TRY(dev_alloc(s, &B.fk, 3 * (int64_t)G * m.Kp, "removal factors"));
-    m.rows = row_shape(N, D, rows, (int64_t)n_rows[1], K);
-    if (m.rows.Kw > 0) {
-        TRY(dev_alloc(s, &B.pw, rows * m.rows.Kw, "weight rows"));
-        TRY(dev_alloc(s, &B.rho, rows * m.rows.Kw, "weight rows"));
-        TRY(dev_alloc(s, &B.fz, 2 * (int64_t)G * m.Kp, "topic constants"));
-        TRY(dev_alloc(s, &B.order_len, D, "document order"));
-        TRY_HIP(launch_doc_order(m, B.doc_off, B.order_len, s->st));
-    }
-    TRY(dev_alloc(s, &B.rep_part, rows, "repair partial counts"));
-    TRY(dev_alloc(s, &B.part, stat_partials_needed(), "reduction partials"));
+    const int64_t gk = (int64_t)G * m.Kp, vk = (int64_t)V * m.Kp;
+    B.partial_len = loglik_partials_needed();
     {
-        TRY(dev_alloc(s, &B.exact, 1, "sampler context"));
+        Arrays a;
+        a.add(&B.logS, n_logS);
+        a.add(&B.Q, n_Q);
+        a.add(&B.Q64, n_Q);
+        a.add(&B.lfact, (int64_t)m.ncap + 1);
+        a.add(&B.nt, rows * m.Kp);
+        a.add(&B.nt16, n16);
+        a.add(&B.B, vk);
+        a.add(&B.B16, vk);
+        a.add(&B.wide, 1);
+        a.add(&B.Ngk, gk);
+        a.add(&B.Tgk, gk);
+        a.add(&B.Bk, m.Kp);
+        a.add(&B.f0, gk);
+        a.add(&B.f1, gk);
+        a.add(&B.fk, 3 * gk);
+        a.add(&B.part, stat_partials_needed());
+        a.add(&B.exact, 1);
+        a.add(&B.partial, B.partial_len);
+        if (m.rows.Kw > 0) {
+            a.add(&B.pw, rows * m.rows.Kw);
+            a.add(&B.rho, rows * m.rows.Kw);
+            a.add(&B.fz, 2 * gk);
+            a.add(&B.order_len, D);
+        }
+        TRY(a.alloc(s, "the count state and its tables"));
+    }
+    TRY_HIP(launch_stirling(m, B.logS, B.Q, B.Q64, B.lfact, s->st));
+    TRY_HIP(launch_fill_i32(B.nt, rows * m.Kp, 0, s->st));
+    TRY_HIP(launch_fill_i32(reinterpret_cast<int32_t *>(B.nt16), n16 / 2, 0, s->st));
+    if (m.rows.Kw > 0) TRY_HIP(launch_doc_order(m, B.doc_off, B.order_len, s->st));
+    {
         ExactCtx x{};
         x.Ngk = B.Ngk;
         x.Tgk = B.Tgk;
@@ -532,8 +548,6 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         TRY_HIP(hipMemcpyAsync(B.exact, &x, sizeof x, hipMemcpyHostToDevice, s->st));
         TRY_HIP(hipStreamSynchronize(s->st));
     }
-    B.partial_len = loglik_partials_needed();
-    TRY(dev_alloc(s, &B.partial, B.partial_len, "loglik partials"));
     s->cur = 0;
     TRY_HIP(launch_init_z(m, corpus->init_seed, B.zr[0], s->st));
     TRY(rebuild_state(s));

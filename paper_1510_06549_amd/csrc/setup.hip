@@ -72,16 +72,35 @@ __global__ void k_make_gw(int32_t D, int32_t V, int32_t G, const int32_t *__rest
 // ------------------------------------------------------------ narrow rows
 // A row is narrow if its (group, word) pair occurs at most kNarrowMax times:
 // no count of the row can then exceed kNarrowMax.
-__global__ void k_row_narrow(int64_t rows, const int32_t *__restrict__ gw_count,
-                             uint8_t *__restrict__ row_narrow, unsigned long long *__restrict__ n)
+// The two counters get one pair of atomics per block, from a grid of a few
+// blocks per compute unit (a pair per wavefront: 178 us for 468 000 rows).
+__global__ void __launch_bounds__(kBlock) k_row_narrow(int64_t rows,
+                                                       const int32_t *__restrict__ gw_count,
+                                                       uint8_t *__restrict__ row_narrow,
+                                                       unsigned long long *__restrict__ n)
 {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool nar = q < rows && gw_count[q] <= kNarrowMax;
-    if (q < rows) row_narrow[q] = nar ? 1 : 0;
-    const unsigned long long c = __popcll(__ballot(nar));
-    const unsigned long long u = __popcll(__ballot(q < rows && gw_count[q] > 0));
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(n, c);
-    if ((threadIdx.x & 63) == 0 && u) atomicAdd(n + 1, u);
+    __shared__ int32_t sum[2];
+    if (threadIdx.x < 2) sum[threadIdx.x] = 0;
+    __syncthreads();
+    int32_t c = 0, u = 0;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < rows; q += stride) {
+        const int32_t have = gw_count[q];
+        row_narrow[q] = have <= kNarrowMax ? 1 : 0;
+        c += have <= kNarrowMax;
+        u += have > 0;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        c += __shfl_xor(c, o);
+        u += __shfl_xor(u, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&sum[0], c);
+        atomicAdd(&sum[1], u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && sum[threadIdx.x])
+        atomicAdd(n + threadIdx.x, (unsigned long long)sum[threadIdx.x]);
 }
 
 __global__ void k_tok_narrow(int64_t N, const int32_t *__restrict__ gw,
@@ -100,40 +119,59 @@ __global__ void k_max_i32(const int32_t *__restrict__ x, int64_t n, int32_t *__r
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
         m = max(m, x[i]);
     for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, m);
+    __shared__ int32_t wave[kBlock / 64];
+    if ((threadIdx.x & 63) == 0) wave[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / 64; ++w) m = max(m, wave[w]);
+        atomicMax(out, m);
+    }
 }
 
 // --------------------------------------------------------------- Stirling
-// One workgroup walks the rows: row n + 1 from row n,
+// Row n + 1 from row n,
 //   S^{n+1}_t = S^n_{t-1} + (n - t a) S^n_t,  S^n_0 = [n == 0],  S^n_t = 0 (t > n),
-// in log space (log-sum-exp of the two terms).
-__global__ void __launch_bounds__(1024) k_stirling_rows(int32_t nmax, double a,
-                                                        double *__restrict__ logS)
+// in log space (log-sum-exp of the two terms).  A launch takes kBand rows, a
+// block the columns [t0, t0 + kBandCols) of them: an entry needs the one above
+// and the one left of it, so the block also forms the kBand columns left of its
+// own, one fewer each row, and blocks are independent.  The rows are a chain of
+// exp and log1p either way; one workgroup for all columns was bound by its own
+// compute unit instead (ncap = 808: 1.37 ms, now 0.62; 2 630: 9.1 ms, now 2.0).
+// The logarithm of the factor does not depend on the chain and is taken a row ahead.
+constexpr int kBand = 64, kBandCols = 192;
+__global__ void __launch_bounds__(kBand + kBandCols) k_stirling_rows(int32_t n0, int32_t nmax,
+                                                                     double a,
+                                                                     double *__restrict__ logS)
 {
-    if (threadIdx.x == 0) logS[0] = 0.0;
+    __shared__ double row[2][kBand + kBandCols + 1];
+    const int32_t c = threadIdx.x;
+    const int32_t t = (int32_t)blockIdx.x * kBandCols - kBand + c;  // this thread's column
+    const int32_t rows = nmax - n0 < kBand ? nmax - n0 : kBand;
+    if (c == 0) row[0][0] = row[1][0] = -INFINITY;
+    double same = -INFINITY;
+    if (t >= 0 && t <= n0) same = n0 == 0 ? 0.0 : logS[tri_index(n0, t)];
+    if (n0 == 0 && t == 0 && c >= kBand) logS[0] = 0.0;
+    row[0][c + 1] = same;
+    // log(n - t a) of the row being formed from row n (used only for t <= n)
+    double factor = t >= 0 && t <= n0 ? log((double)n0 - (double)t * a) : 0.0;
     __syncthreads();
-    for (int64_t n = 0; n < nmax; ++n) {
-        const double *row = logS + tri_index(n, 0);
-        double *next = logS + tri_index(n + 1, 0);
-        for (int64_t t = threadIdx.x; t <= n + 1; t += blockDim.x) {
-            double v;
-            if (t == 0) {
-                v = -INFINITY;
-            } else {
-                const double left = row[t - 1];
-                const double same = (t <= n) ? row[t] : -INFINITY;
-                const double term = (same == -INFINITY) ? -INFINITY
-                                                        : same + log((double)n - (double)t * a);
-                if (left == -INFINITY) v = term;
-                else if (term == -INFINITY) v = left;
-                else {
-                    const double hi = fmax(left, term), lo = fmin(left, term);
-                    v = hi + log1p(exp(lo - hi));
-                }
+    for (int32_t i = 0; i < rows; ++i) {
+        const int32_t n = n0 + i;
+        const double left = row[i & 1][c];
+        double v = -INFINITY;
+        if (t > 0 && t <= n + 1) {
+            const double term = (t > n || same == -INFINITY) ? -INFINITY : same + factor;
+            if (left == -INFINITY) v = term;
+            else if (term == -INFINITY) v = left;
+            else {
+                const double hi = fmax(left, term), lo = fmin(left, term);
+                v = hi + log1p(exp(lo - hi));
             }
-            next[t] = v;
         }
-        __threadfence_block();
+        if (t >= 0 && t <= n + 1) factor = log((double)(n + 1) - (double)t * a);
+        same = v;
+        row[(i + 1) & 1][c + 1] = v;
+        if (c >= kBand && t <= n + 1) logS[tri_index(n + 1, t)] = v;
         __syncthreads();
     }
 }
@@ -404,7 +442,7 @@ hipError_t launch_make_gw(const Model &m, const int32_t *words, const int64_t *d
 hipError_t launch_max_i32(const int32_t *x, int64_t n, int32_t *out, hipStream_t st)
 {
     int64_t nb = blocks_for(n, kBlock);
-    if (nb > 4096) nb = 4096;
+    if (nb > 1024) nb = 1024;
     hipLaunchKernelGGL(k_max_i32, dim3((unsigned)nb), dim3(kBlock), 0, st, x, n, out);
     return hipGetLastError();
 }
@@ -413,7 +451,11 @@ hipError_t launch_stirling(const Model &m, double *logS, float2 *Q, double2 *Q64
                            hipStream_t st)
 {
     const int32_t nmax = m.ncap;  // rows 0..ncap of log S; pairs for n < ncap
-    hipLaunchKernelGGL(k_stirling_rows, dim3(1), dim3(1024), 0, st, nmax, m.a, logS);
+    for (int32_t n0 = 0; n0 < nmax; n0 += kBand) {
+        const int32_t last = nmax - n0 < kBand ? nmax : n0 + kBand;  // columns 0 .. last
+        hipLaunchKernelGGL(k_stirling_rows, dim3((unsigned)(last / kBandCols + 1)),
+                           dim3(kBand + kBandCols), 0, st, n0, nmax, m.a, logS);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)blocks_for(nmax, kBlock), (unsigned)nmax);
@@ -530,8 +572,9 @@ hipError_t launch_narrow_flags(const Model &m, const int32_t *gw, const int32_t 
                                unsigned long long *n_narrow, hipStream_t st)
 {
     const int64_t rows = (int64_t)m.G * m.V;
-    hipLaunchKernelGGL(k_row_narrow, dim3((unsigned)blocks_for(rows, kBlock)), dim3(kBlock), 0, st,
-                       rows, gw_count, row_narrow, n_narrow);
+    const unsigned nb = (unsigned)std::min<int64_t>(blocks_for(rows, kBlock), 1024);
+    hipLaunchKernelGGL(k_row_narrow, dim3(nb), dim3(kBlock), 0, st, rows,
+                       gw_count, row_narrow, n_narrow);
     if (m.N > 0)
         hipLaunchKernelGGL(k_tok_narrow, dim3((unsigned)blocks_for(m.N, kBlock)), dim3(kBlock), 0,
                            st, m.N, gw, row_narrow, tok_narrow);

@@ -192,7 +192,7 @@ struct DeviceBuffers {
     double *partial = nullptr;    // loglik block partials
     int64_t partial_len = 0;
     int32_t *err = nullptr;       // [2] device error flags
-    double *scalar = nullptr;     // [1] reduction result
+    double *scalar = nullptr;     // [2] reduction result, its error flag
     ExactCtx *exact = nullptr;    // [1] the sampler's fp64 re-decision inputs
     // debug-conditional buffers (allocated on demand)
     int32_t *zr_dbg = nullptr;
@@ -236,8 +236,11 @@ hipError_t launch_pack_zr(const Model &m, const int32_t *z, const uint8_t *r, in
                           int32_t *bad, hipStream_t st);
 hipError_t launch_unpack_zr(const Model &m, const int32_t *zr, int32_t *z, uint8_t *r,
                             hipStream_t st);
-hipError_t build_row_index(const Model &m, DeviceBuffers &b, const int32_t *gw_count,
+// tokens grouped by row, row offsets and the state route; gw_count [rows + 1]
+// (its last entry 0) is used up, tmp holds row_index_scratch(N, rows) ints
+hipError_t build_row_index(const Model &m, DeviceBuffers &b, int32_t *gw_count, int32_t *tmp,
                            hipStream_t st);
+int64_t row_index_scratch(int64_t N, int64_t rows);
 // count rows with the repair, and the shadow-base counts B (zeroed, then each
 // row's table counts added) of the plain model, from the state zr; the totals
 // N_gk and T_gk are zeroed too
