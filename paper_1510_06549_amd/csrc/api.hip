@@ -113,7 +113,7 @@ private:
         void **p;
         size_t at;
     };
-    Part parts_[24] = {};  // the largest list has 22 arrays
+    Part parts_[24] = {};  // the largest list has 23 arrays
     int n_ = 0;
     size_t total_ = 0;
 };
@@ -497,6 +497,7 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         a.add(&B.Q, n_Q);
         a.add(&B.Q64, n_Q);
         a.add(&B.lfact, (int64_t)m.ncap + 1);
+        a.add(&B.lgt, 3 * kLgammaTable);
         a.add(&B.nt, rows * m.Kp);
         a.add(&B.nt16, n16);
         a.add(&B.B, vk);
@@ -520,6 +521,7 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         TRY(a.alloc(s, "the count state and its tables"));
     }
     TRY_HIP(launch_stirling(m, B.logS, B.Q, B.Q64, B.lfact, s->st));
+    TRY_HIP(launch_lgamma_table(m, B.lgt, s->st));
     TRY_HIP(launch_fill_i32(B.nt, rows * m.Kp, 0, s->st));
     TRY_HIP(launch_fill_i32(reinterpret_cast<int32_t *>(B.nt16), n16 / 2, 0, s->st));
     if (m.rows.Kw > 0) TRY_HIP(launch_doc_order(m, B.doc_off, B.order_len, s->st));
@@ -696,16 +698,13 @@ int spdp_loglik(spdp_state *s, double *out)
 {
     if (!s || !out) return fail(SPDP_E_ARG, "null argument");
     HIP_TRY(hipSetDevice(s->device));
-    HIP_TRY(widen_rows(s));
-    HIP_TRY(launch_fill_i32(s->b.err, 2, 0, s->st));
     HIP_TRY(launch_loglik(s->m, s->b, s->b.zr[s->cur], s->st));
-    double v = 0.0;
-    HIP_TRY(hipMemcpyAsync(&v, s->b.scalar, sizeof v, hipMemcpyDeviceToHost, s->st));
-    int32_t herr[2];
-    int rc = check_device_flags(s, herr);
+    double v[2] = {0.0, 0.0};  // the value, and 1 if a cell has no probability
+    HIP_TRY(hipMemcpyAsync(v, s->b.scalar, sizeof v, hipMemcpyDeviceToHost, s->st));
+    int rc = sync(s);
     if (rc != SPDP_OK) return rc;
-    if (herr[0]) return fail(SPDP_E_STATE, "count state has a cell with t > n or t = 0 < n");
-    *out = v;
+    if (v[1] != 0.0) return fail(SPDP_E_STATE, "count state has a cell with t > n or t = 0 < n");
+    *out = v[0];
     return SPDP_OK;
 }
 

@@ -189,7 +189,9 @@ struct DeviceBuffers {
     uint32_t *rep_part = nullptr; // [G V] heads promoted per row in the last rebuild
     unsigned long long *part = nullptr; // reduction partials
     unsigned long long *ctr = nullptr;  // [4] changed, repaired (filled on demand)
-    double *partial = nullptr;    // loglik block partials
+    double *lgt = nullptr;        // [3][kLgammaTable] lgamma(x + c) - lgamma(x), x = alpha,
+                                  // gamma, K alpha
+    double *partial = nullptr;    // loglik block partials and flags
     int64_t partial_len = 0;
     int32_t *err = nullptr;       // [2] device error flags
     double *scalar = nullptr;     // [2] reduction result, its error flag
@@ -305,6 +307,8 @@ hipError_t launch_sample_async(const Model &m, const DeviceBuffers &b, const int
                                const int32_t *tok_doc, int32_t *cdk, int32_t *zr, uint32_t sweep,
                                uint64_t seed, int32_t waves, bool live_totals, hipStream_t st);
 int64_t loglik_partials_needed();
+constexpr int kLgammaTable = 1024;
+hipError_t launch_lgamma_table(const Model &m, double *lgt, hipStream_t st);
 
 hipError_t launch_theta(const Model &m, const DeviceBuffers &b, const int32_t *zr, double *theta,
                         hipStream_t st);
