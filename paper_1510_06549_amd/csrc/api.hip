@@ -448,7 +448,8 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         e = hipMemcpyAsync(B.doc_group, groups->doc_group, (size_t)D * sizeof(int32_t),
                            hipMemcpyHostToDevice, s->st);
     if (e == hipSuccess) e = launch_fill_i32(gw_count, rows + 1, 0, s->st);
-    if (e == hipSuccess) e = launch_make_gw(m, words_d, B.doc_off, B.doc_group, B.gw, gw_count, B.err, s->st);
+    if (e == hipSuccess) e = launch_make_gw(m, D, words_d, B.doc_off, B.doc_group, B.gw, gw_count,
+                                            B.err, s->st);
     if (e == hipSuccess) e = launch_max_i32(gw_count, rows, B.err + 1, s->st);
     int32_t herr[2] = {0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(herr, B.err, sizeof herr, hipMemcpyDeviceToHost, s->st);
@@ -766,30 +767,27 @@ int spdp_heldout(spdp_state *s, const spdp_corpus *test, const spdp_groups *test
         return fail(SPDP_E_ARG, "null test array");
     if (test->doc_offsets[0] != 0 || test->doc_offsets[D] != N)
         return fail(SPDP_E_ARG, "test doc_offsets must run from 0 to n_tokens");
-    std::vector<int32_t> gw((size_t)(N > 0 ? N : 1));
     for (int32_t d = 0; d < D; ++d) {
-        const int64_t b0 = test->doc_offsets[d], b1 = test->doc_offsets[d + 1];
-        const int32_t g = test_groups->doc_group[d];
-        if (b1 < b0) return fail(SPDP_E_ARG, "test doc_offsets decrease");
-        if (g < 0 || g >= m.G) return fail(SPDP_E_ARG, "test doc_group out of [0, n_groups)");
-        for (int64_t i = b0; i < b1; ++i) {
-            const int32_t w = test->words[i];
-            if (w < 0 || w >= m.V) return fail(SPDP_E_ARG, "test word id out of [0, vocab)");
-            gw[(size_t)i] = g * m.V + w;
-        }
+        if (test->doc_offsets[d + 1] < test->doc_offsets[d])
+            return fail(SPDP_E_ARG, "test doc_offsets decrease");
+        if (test_groups->doc_group[d] < 0 || test_groups->doc_group[d] >= m.G)
+            return fail(SPDP_E_ARG, "test doc_group out of [0, n_groups)");
     }
     HIP_TRY(hipSetDevice(s->device));
     HIP_TRY(widen_rows(s));
-    int32_t *gw_d = nullptr, *grp_d = nullptr, *z_d = nullptr;
-    int64_t *off_d = nullptr;
-    double *ll_d = nullptr;
-    hipError_t e = hipMalloc(&gw_d, (size_t)(N > 0 ? N : 1) * 4);
-    if (e == hipSuccess) e = hipMalloc(&z_d, (size_t)(N > 0 ? N : 1) * 4);
-    if (e == hipSuccess) e = hipMalloc(&off_d, (size_t)(D + 1) * 8);
-    if (e == hipSuccess) e = hipMalloc(&grp_d, (size_t)(D > 0 ? D : 1) * 4);
-    if (e == hipSuccess) e = hipMalloc(&ll_d, (size_t)(D > 0 ? D : 1) * 8);
+    std::vector<double> ll((size_t)(D > 0 ? D : 1), 0.0);
+    // one allocation: document sums, offsets and groups, rows, topics
+    char *all = nullptr;
+    const size_t nn = (size_t)(N > 0 ? N : 1), nd = (size_t)D + 1;
+    HIP_TRY(hipMalloc(&all, nd * (8 + 8 + 4) + nn * (4 + 4)));
+    double *ll_d = reinterpret_cast<double *>(all);
+    int64_t *off_d = reinterpret_cast<int64_t *>(ll_d + nd);
+    int32_t *grp_d = reinterpret_cast<int32_t *>(off_d + nd);
+    int32_t *gw_d = grp_d + nd, *z_d = gw_d + nn;
+    // the words are validated and turned into rows on the device
+    hipError_t e = launch_fill_i32(s->b.err, 2, 0, s->st);
     if (e == hipSuccess && N > 0)
-        e = hipMemcpyAsync(gw_d, gw.data(), (size_t)N * 4, hipMemcpyHostToDevice, s->st);
+        e = hipMemcpyAsync(gw_d, test->words, (size_t)N * 4, hipMemcpyHostToDevice, s->st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(off_d, test->doc_offsets, (size_t)(D + 1) * 8, hipMemcpyHostToDevice,
                            s->st);
@@ -797,20 +795,23 @@ int spdp_heldout(spdp_state *s, const spdp_corpus *test, const spdp_groups *test
         e = hipMemcpyAsync(grp_d, test_groups->doc_group, (size_t)D * 4, hipMemcpyHostToDevice,
                            s->st);
     if (e == hipSuccess)
-        e = launch_foldin(m, s->b, D, gw_d, off_d, grp_d, n_sweeps, seed, z_d, ll_d, s->st);
-    std::vector<double> ll((size_t)(D > 0 ? D : 1), 0.0);
-    if (e == hipSuccess && D > 0)
-        e = hipMemcpyAsync(ll.data(), ll_d, (size_t)D * 8, hipMemcpyDeviceToHost, s->st);
-    if (e == hipSuccess && z_out && N > 0)
-        e = hipMemcpyAsync(z_out, z_d, (size_t)N * 4,
-                           where ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->st);
+        e = launch_make_gw(m, D, gw_d, off_d, grp_d, gw_d, nullptr, s->b.err, s->st);
+    int32_t bad = 0;
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(&bad, s->b.err, sizeof bad, hipMemcpyDeviceToHost, s->st);
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);
-    (void)hipFree(gw_d);
-    (void)hipFree(z_d);
-    (void)hipFree(off_d);
-    (void)hipFree(grp_d);
-    (void)hipFree(ll_d);
+    if (e == hipSuccess && !bad) {
+        e = launch_foldin(m, s->b, D, gw_d, off_d, grp_d, n_sweeps, seed, z_d, ll_d, s->st);
+        if (e == hipSuccess && D > 0)
+            e = hipMemcpyAsync(ll.data(), ll_d, (size_t)D * 8, hipMemcpyDeviceToHost, s->st);
+        if (e == hipSuccess && z_out && N > 0)
+            e = hipMemcpyAsync(z_out, z_d, (size_t)N * 4,
+                               where ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->st);
+        if (e == hipSuccess) e = hipStreamSynchronize(s->st);
+    }
+    (void)hipFree(all);
     HIP_TRY(e);
+    if (bad) return fail(SPDP_E_ARG, "test word id out of [0, vocab)");
     double total = 0.0;  // documents in order
     for (int32_t d = 0; d < D; ++d) total += ll[(size_t)d];
     out2[0] = N > 0 ? exp(-total / (double)N) : NAN;

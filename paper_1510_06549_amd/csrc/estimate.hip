@@ -267,12 +267,11 @@ __device__ __forceinline__ void load_fold_rows(const FoldArgs &A, int32_t q, int
 // slot order, of p (gamma + B[v][k]) for p > 0.
 template <int KPL, int SP>
 __device__ __forceinline__ void phi_from_rows(const FoldArgs &A, const FoldRows<KPL, SP> &R,
-                                              int32_t kbase, const double *inv, const double *base,
+                                              const double *inv, const double *base,
                                               double (&ph)[KPL])
 {
 #pragma unroll
     for (int j = 0; j < KPL; ++j) {
-        const int32_t k = kbase + j;
         const double n = (double)(R.n[j] & kCountMax), t = (double)(R.n[j] >> kCountBits);
         double bw;
         if constexpr (SP == 0) {
@@ -283,7 +282,7 @@ __device__ __forceinline__ void phi_from_rows(const FoldArgs &A, const FoldRows<
             for (int s = 0; s < SP; ++s)
                 if (R.p[s] > 0.0) bw += R.p[s] * (A.gamma + (double)R.b[s][j]);
         }
-        ph[j] = (k < A.K) ? (n - A.a * t) * inv[k] + bw * base[k] : 0.0;
+        ph[j] = (n - A.a * t) * inv[j] + bw * base[j];  // padding topics: 0
     }
 }
 
@@ -302,7 +301,7 @@ __device__ __forceinline__ void for_chunk_phi(const FoldArgs &A, int32_t g, int3
             FoldRows<KPL, SP> r;
             load_fold_rows<KPL, SP>(A, __builtin_amdgcn_readlane(gw_c, x), g, kbase, r);
             double ph[KPL];
-            phi_from_rows<KPL, SP>(A, r, kbase, inv, base, ph);
+            phi_from_rows<KPL, SP>(A, r, inv, base, ph);
             f(x, ph);
         }
     } else {
@@ -313,28 +312,36 @@ __device__ __forceinline__ void for_chunk_phi(const FoldArgs &A, int32_t g, int3
             load_fold_rows<KPL, SP>(A, __builtin_amdgcn_readlane(gw_c, x1), g, kbase, rb);
             {
                 double ph[KPL];
-                phi_from_rows<KPL, SP>(A, ra, kbase, inv, base, ph);
+                phi_from_rows<KPL, SP>(A, ra, inv, base, ph);
                 f(x, ph);
             }
             if (x + 1 < nc) {
                 const int32_t x2 = x + 2 < nc ? x + 2 : x + 1;
                 load_fold_rows<KPL, SP>(A, __builtin_amdgcn_readlane(gw_c, x2), g, kbase, ra);
                 double ph[KPL];
-                phi_from_rows<KPL, SP>(A, rb, kbase, inv, base, ph);
+                phi_from_rows<KPL, SP>(A, rb, inv, base, ph);
                 f(x + 1, ph);
             }
         }
     }
 }
 
+// Bound by instructions issued per token (fp64, with a wave scan on the chain
+// from one token to the next).  So each lane takes one of 64 tokens' uniforms,
+// as a uniform token's Philox runs on the scalar unit that four SIMDs share;
+// counts and factors stay in registers, not behind an LDS round trip in the
+// chain; and nothing selects on k < K, as padding topics' factors are zero.
+// 8 000 documents of 200 tokens, K = 200, 10 sweeps (17.6 million draws and
+// sums): 5.9 -> 4.6 ms.
 template <int KPL, int SP>
 __global__ void __launch_bounds__(64) k_foldin(FoldArgs A)
 {
-    // document counts and the group's per-topic factors 1/(b + N) and
-    // (b + a T)/(b + N)/(V gamma + B_k) (zero for padding topics)
+    // this lane's document counts cr, and the group's per-topic factors
+    // 1/(b + N) and (b + a T)/(b + N)/(V gamma + B_k) (zero for padding topics,
+    // whose group estimates and weights are then zero)
     __shared__ int32_t c[64 * KPL];
-    __shared__ double inv[64 * KPL];
-    __shared__ double base[64 * KPL];
+    int32_t cr[KPL];
+    double inv[KPL], base[KPL];
     const int32_t d = blockIdx.x;
     if (d >= A.D) return;
     const int32_t lane = threadIdx.x, kbase = lane * KPL;
@@ -344,12 +351,12 @@ __global__ void __launch_bounds__(64) k_foldin(FoldArgs A)
     for (int j = 0; j < KPL; ++j) {
         const int32_t k = kbase + j;
         c[k] = 0;
-        inv[k] = base[k] = 0.0;
+        inv[j] = base[j] = 0.0;
         if (k < A.K) {
             const double N = (double)A.Ngk[(int64_t)g * A.Kp + k];
             const double T = (double)A.Tgk[(int64_t)g * A.Kp + k];
-            inv[k] = 1.0 / (A.b + N);
-            base[k] = (A.b + A.a * T) / (A.b + N) / (A.Vgamma + (double)A.Bk[k]);
+            inv[j] = 1.0 / (A.b + N);
+            base[j] = (A.b + A.a * T) / (A.b + N) / (A.Vgamma + (double)A.Bk[k]);
         }
     }
     __syncthreads();
@@ -361,6 +368,8 @@ __global__ void __launch_bounds__(64) k_foldin(FoldArgs A)
         atomicAdd(&c[z], 1);
     }
     __syncthreads();
+#pragma unroll
+    for (int j = 0; j < KPL; ++j) cr[j] = c[kbase + j];
 
     for (int32_t s = 0; s < A.n_sweeps; ++s) {
         // 64 tokens at a time: lane l reads and writes token cb + l, so each
@@ -370,23 +379,24 @@ __global__ void __launch_bounds__(64) k_foldin(FoldArgs A)
             const bool mine = lane < nc;
             const int32_t gw_c = mine ? A.gw[cb + lane] : 0;
             int32_t z_c = mine ? A.z[cb + lane] : 0;
+            // the chunk's uniforms, a token each lane
+            const uint32_t x_c = philox_x0(A.seed, (uint64_t)(cb + lane), (uint32_t)s,
+                                           kPurposeFoldin);
             for_chunk_phi<KPL, SP>(A, g, kbase, gw_c, nc, inv, base, [&](int32_t x,
                                                                             const double(&ph)[KPL]) {
-                const int64_t i = cb + x;
                 const int32_t k0 = __builtin_amdgcn_readlane(z_c, x);
                 double pre[KPL];
                 double acc = 0.0;
 #pragma unroll
                 for (int j = 0; j < KPL; ++j) {
-                    const int32_t k = kbase + j;
-                    const double cw = (double)(c[k] - (k == k0 ? 1 : 0)) + A.alpha;
-                    acc += (k < A.K) ? cw * ph[j] : 0.0;
+                    cr[j] -= kbase + j == k0 ? 1 : 0;
+                    acc += ((double)cr[j] + A.alpha) * ph[j];
                     pre[j] = acc;
                 }
                 const double incl = wave_inclusive_sum64(acc);
                 const double excl = wave_shift_right64(incl);
                 const double total = readlane64(incl, 63);
-                const uint32_t xr = philox_x0(A.seed, (uint64_t)i, (uint32_t)s, kPurposeFoldin);
+                const uint32_t xr = (uint32_t)__builtin_amdgcn_readlane((int32_t)x_c, x);
                 const double target = (double)(xr >> 8) * (1.0 / 16777216.0) * total;
                 const double rel = target - excl;
                 int32_t cnt = 0;
@@ -400,22 +410,19 @@ __global__ void __launch_bounds__(64) k_foldin(FoldArgs A)
                 }
                 if (k1 >= A.K) k1 = k0;  // no crossing (rounding at the very top): keep
                 if (lane == x) z_c = k1;
-                if (lane == 0 && k1 != k0) {
-                    c[k0] -= 1;
-                    c[k1] += 1;
-                }
+#pragma unroll
+                for (int j = 0; j < KPL; ++j) cr[j] += kbase + j == k1 ? 1 : 0;
             });
             if (mine) A.z[cb + lane] = z_c;
         }
     }
-    __syncthreads();
 
     // log p(w_d) with theta_d from the final counts
     const double tden = 1.0 / ((double)(end - beg) + (double)A.K * A.alpha);
     double th[KPL];
 #pragma unroll
     for (int j = 0; j < KPL; ++j)
-        th[j] = (kbase + j < A.K) ? ((double)c[kbase + j] + A.alpha) * tden : 0.0;
+        th[j] = (kbase + j < A.K) ? ((double)cr[j] + A.alpha) * tden : 0.0;
     double ll = 0.0;
     for (int64_t cb = beg; cb < end; cb += 64) {
         const int32_t nc = (int32_t)min((int64_t)64, end - cb);

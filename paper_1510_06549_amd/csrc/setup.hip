@@ -43,9 +43,9 @@ hipError_t fill(T *p, int64_t n, T v, hipStream_t st)
 
 // ---------------------------------------------------------------- make_gw
 // One block per document: row index per token, validation, per-row counts.
-__global__ void k_make_gw(int32_t D, int32_t V, int32_t G, const int32_t *__restrict__ words,
+__global__ void k_make_gw(int32_t D, int32_t V, int32_t G, const int32_t *words,
                           const int64_t *__restrict__ doc_off, const int32_t *__restrict__ doc_group,
-                          int32_t *__restrict__ gw, int32_t *__restrict__ gw_count,
+                          int32_t *gw, int32_t *__restrict__ gw_count,
                           int32_t *__restrict__ bad)
 {
     const int32_t d = blockIdx.x;
@@ -65,7 +65,7 @@ __global__ void k_make_gw(int32_t D, int32_t V, int32_t G, const int32_t *__rest
         }
         const int32_t q = g * V + w;
         gw[i] = q;
-        atomicAdd(gw_count + q, 1);
+        if (gw_count) atomicAdd(gw_count + q, 1);
     }
 }
 
@@ -429,13 +429,13 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
     return fill(p, n, v, st);
 }
 
-hipError_t launch_make_gw(const Model &m, const int32_t *words, const int64_t *doc_off,
+hipError_t launch_make_gw(const Model &m, int32_t D, const int32_t *words, const int64_t *doc_off,
                           const int32_t *doc_group, int32_t *gw, int32_t *gw_count, int32_t *bad,
                           hipStream_t st)
 {
-    if (m.D <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_make_gw, dim3(m.D), dim3(kBlock), 0, st, m.D, m.V, m.G, words, doc_off,
-                       doc_group, gw, gw_count, bad);
+    if (D <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_make_gw, dim3((unsigned)D), dim3(kBlock), 0, st, D, m.V, m.G, words,
+                       doc_off, doc_group, gw, gw_count, bad);
     return hipGetLastError();
 }
 

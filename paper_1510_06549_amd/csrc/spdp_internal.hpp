@@ -221,7 +221,10 @@ struct DeviceBuffers {
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t st);
-hipError_t launch_make_gw(const Model &m, const int32_t *words, const int64_t *doc_off,
+// row indices g V + w of D documents' tokens (gw may be words), and the rows'
+// token counts added to gw_count unless it is null; *bad |= 1 for a group, 2
+// for a word out of range
+hipError_t launch_make_gw(const Model &m, int32_t D, const int32_t *words, const int64_t *doc_off,
                           const int32_t *doc_group, int32_t *gw, int32_t *gw_count,
                           int32_t *bad, hipStream_t st);
 hipError_t launch_max_i32(const int32_t *x, int64_t n, int32_t *out, hipStream_t st);
