@@ -55,6 +55,14 @@ def narrow_fraction(cp) -> float:
     return float(np.mean(c[q] <= 255)) if len(q) else 0.0
 
 
+def used_rows(cp) -> int:
+    """(group, word) pairs that have tokens."""
+    import numpy as np
+
+    q = np.repeat(cp.doc_group, np.diff(cp.doc_off)).astype(np.int64) * cp.vocab + cp.words
+    return int(np.count_nonzero(np.bincount(q)))
+
+
 def sample_bytes_per_token(K: int, wide: bool, narrow: float = 0.0) -> float:
     """Bytes the sampling kernel must move per token in this library's layout:
     the K-cell count row of (group, word) (customers and tables packed in one
@@ -63,6 +71,13 @@ def sample_bytes_per_token(K: int, wide: bool, narrow: float = 0.0) -> float:
     counts, or int32 once some count exceeds 65535), and the token stream
     (row index, state and narrow-row flag in, state out)."""
     return (4 - 2 * narrow) * K + (4 if wide else 2) * K + 13
+
+
+def weight_row_bytes_per_token(K: int, n_tokens: int, rows_used: int) -> float:
+    """The same for a sweep over weight rows: the K fp32 weights of the token's
+    row and the token stream, and per row with tokens, once a sweep, its packed
+    counts and shadow-base counts in and two fp32 values per topic out."""
+    return 4 * K + 13 + 16 * K * rows_used / max(n_tokens, 1)
 
 
 def assoc_bytes_per_token(K: int, wide: bool, mean_sources: float, Sp: int,
@@ -509,8 +524,14 @@ def main():
     value = N * args.steps / elapsed
     ms_sample, n_sample = kt["sample"]
     avg_sample_s = ms_sample / 1000.0 / max(n_sample, 1)
+    # a sweep over weight rows makes no 16-bit copy of the shadow base
+    weight_rows = not args.async_sweep and kt["base"][1] == 0
     if args.async_sweep:
         bpt = async_bytes_per_token(wl.K)
+        traffic = None
+    elif weight_rows and assoc is None:
+        narrow = narrow_fraction(cp)
+        bpt = weight_row_bytes_per_token(wl.K, N, used_rows(cp))
         traffic = None
     elif assoc is None:
         narrow = narrow_fraction(cp)
@@ -524,14 +545,17 @@ def main():
         Sp = 1 if s.S <= 1 else (2 if s.S <= 2 else (4 if s.S <= 4 else 8))
         narrow = narrow_fraction(cp)
         bpt = assoc_bytes_per_token(wl.K, wide, mean_sources, Sp, narrow)
+        if weight_rows:
+            bpt = weight_row_bytes_per_token(wl.K, N, used_rows(cp)) + 8 * Sp
         traffic = (recorded_traffic("k_sample_assoc", f"{wl.name}-assoc{args.assoc}")
-                   if args.assoc_eps == 0.3 else None)
+                   if args.assoc_eps == 0.3 and not weight_rows else None)
     alg = N * bpt
     achieved = alg / avg_sample_s / 1e9
     roofline = {
         "bound": "hbm",
         "kernel": ("k_sample_async" if args.async_sweep
-                   else ("k_sample" if assoc is None else "k_sample_assoc")),
+                   else "k_weights + k_sample_rows" if weight_rows
+                   else "k_sample" if assoc is None else "k_sample_assoc"),
         "achieved": round(achieved, 1),
         "peak": HBM_PEAK_GBS,
         "unit": "GB/s",
@@ -547,10 +571,11 @@ def main():
         pass
     elif assoc is None:
         roofline["narrow_row_token_share"] = round(narrow, 4)
-        # context: the same launch time in the bytes of the layout without
-        # narrow rows (32-bit count rows for every token)
-        roofline["all_rows_32bit_equiv_GBps"] = round(
-            N * sample_bytes_per_token(wl.K, wide, 0.0) / avg_sample_s / 1e9, 1)
+        if not weight_rows:
+            # context: the same launch time in the bytes of the layout without
+            # narrow rows (32-bit count rows for every token)
+            roofline["all_rows_32bit_equiv_GBps"] = round(
+                N * sample_bytes_per_token(wl.K, wide, 0.0) / avg_sample_s / 1e9, 1)
         roofline["dense_int32_bytes_per_token"] = dense_bytes_per_token(wl.K)
         roofline["dense_int32_equiv_GBps"] = round(
             N * dense_bytes_per_token(wl.K) / avg_sample_s / 1e9, 1)
