@@ -114,12 +114,20 @@ __global__ void __launch_bounds__(64) k_theta(int32_t D, int32_t K, double alpha
     }
 }
 
-// x / d with r = 1 / d (correctly rounded): the quotient by r, then one
-// correction with the exact remainder, which rounds as the division does
-// (Markstein, "Computation of elementary functions on the IBM RISC System/6000
-// processor", 1990).
+// 1 / d (correctly rounded) for div_by, or 0 where that reciprocal does not
+// serve: it overflows for a subnormal d (a tiny b or gamma with no customer) and
+// is 0 for an infinite one.  The line leaves the quotient and its remainder room.
+__device__ __forceinline__ double reciprocal(double d)
+{
+    return d >= 0x1p-900 && d <= 0x1p900 ? 1.0 / d : 0.0;
+}
+
+// x / d with r = reciprocal(d): the quotient by r, then one correction with the
+// exact remainder, which rounds as the division does (Markstein, "Computation of
+// elementary functions on the IBM RISC System/6000 processor", 1990).
 __device__ __forceinline__ double div_by(double x, double d, double r)
 {
+    if (r == 0.0) return x / d;
     const double q = x * r;
     return __fma_rn(__fma_rn(-q, d, x), r, q);
 }
@@ -150,13 +158,13 @@ __global__ void __launch_bounds__(kPhiBlock) k_phi(PhiArgs A)
     const int32_t k = blockIdx.y * blockDim.x + threadIdx.x;
     if (k >= A.K) return;
     const int32_t g = A.g_begin + (int32_t)blockIdx.z;
-    const double d0 = A.Vgamma + (double)A.Bk[k], r0 = 1.0 / d0;
+    const double d0 = A.Vgamma + (double)A.Bk[k], r0 = reciprocal(d0);
     double dg = 1.0, wg = 0.0;
     if (A.phi) {
         dg = A.b + (double)A.Ngk[(int64_t)g * A.Kp + k];
         wg = A.b + A.a * (double)A.Tgk[(int64_t)g * A.Kp + k];
     }
-    const double rg = 1.0 / dg;
+    const double rg = reciprocal(dg);
     const bool first = A.phi0 != nullptr && blockIdx.z == 0;
     double *out = A.phi ? A.phi + (int64_t)blockIdx.z * A.V * A.K : nullptr;
     // kPhiWords consecutive words per thread, their loads together (words past

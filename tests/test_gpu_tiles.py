@@ -8,6 +8,10 @@
   takes, with rows of both widths, and a document count that is no multiple of
   the documents a wave takes (relative 1e-13 / 1e-12, as for the other
   estimate tests: each value is one fp64 expression).
+* Estimates whose divisors b + N and V gamma + B_k have no reciprocal in fp64
+  (subnormal or infinite, for topics and groups without customers) or lie at
+  the ends of the range where one is used; the same tolerances, and a few
+  subnormal units (8 x 5e-324) where the values themselves are subnormal.
 """
 import numpy as np
 import pytest
@@ -50,4 +54,28 @@ def test_estimates_at_range_edges(K, S):
     np.testing.assert_allclose(th, th_o, rtol=1e-13)
     np.testing.assert_allclose(p0, p0_o.T, rtol=1e-13)
     np.testing.assert_allclose(pg, pg_o.transpose(0, 2, 1), rtol=1e-12)
+    s.close()
+
+
+@pytest.mark.parametrize("b,gamma", [(1e-310, 0.01), (20.0, 1e-320), (5e-324, 5e-324),
+                                     (1e-280, 1e-290), (1e308, 0.01), (20.0, 1e308),
+                                     (1e270, 1e265), (1e275, 1e-275)])
+@pytest.mark.parametrize("S", [0, 2])
+def test_estimates_with_extreme_divisors(b, gamma, S):
+    print(f"estimates b={b} gamma={gamma} sources={S}", flush=True)
+    V, K = 13, 70  # fewer tokens than topics, so most topics have no customer
+    rng = np.random.default_rng(4)
+    cp = synth.Corpus(rng.integers(0, V, 20).astype(np.int32), np.array([0, 9, 20]),
+                      np.array([0, 1], np.int32), np.zeros(20, np.int32), np.zeros(20, np.uint8),
+                      2, V)
+    wl = synth.workload(0)
+    wl = type(wl)(**{**wl.__dict__, "b": b, "gamma": gamma})
+    assoc = synth.associations(2, V, S, 0.3, 5) if S else None
+    s, m = parity.make_pair(cp, wl, K=K, assoc=assoc)
+    st = parity.state_of(s, m)
+    _, p0_o, pg_o = m.estimates(st[0], m.rebuild(*st))
+    _, p0, pg = s.estimates()
+    assert np.array_equal(np.isnan(p0), np.isnan(p0_o.T))
+    np.testing.assert_allclose(p0, p0_o.T, rtol=1e-13, atol=4e-323)
+    np.testing.assert_allclose(pg, pg_o.transpose(0, 2, 1), rtol=1e-12, atol=4e-323)
     s.close()
