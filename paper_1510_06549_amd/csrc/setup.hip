@@ -42,30 +42,32 @@ hipError_t fill(T *p, int64_t n, T v, hipStream_t st)
 }
 
 // ---------------------------------------------------------------- make_gw
-// One block per document: row index per token, validation, per-row counts.
+// One block per document at a time: row index per token, validation, per-row
+// counts.  The grid is bounded, as a launch takes fewer than 2^32 threads.
+constexpr int32_t kGwBlocks = 1 << 20;
 __global__ void k_make_gw(int32_t D, int32_t V, int32_t G, const int32_t *words,
                           const int64_t *__restrict__ doc_off, const int32_t *__restrict__ doc_group,
                           int32_t *gw, int32_t *__restrict__ gw_count,
                           int32_t *__restrict__ bad)
 {
-    const int32_t d = blockIdx.x;
-    if (d >= D) return;
-    const int32_t g = doc_group[d];
-    const int64_t beg = doc_off[d], end = doc_off[d + 1];
-    if (g < 0 || g >= G) {
-        if (threadIdx.x == 0) atomicOr(bad, 1);
-        return;
-    }
-    for (int64_t i = beg + threadIdx.x; i < end; i += blockDim.x) {
-        const int32_t w = words[i];
-        if (w < 0 || w >= V) {
-            atomicOr(bad, 2);
-            gw[i] = 0;
+    for (int64_t d = blockIdx.x; d < D; d += gridDim.x) {
+        const int32_t g = doc_group[d];
+        const int64_t beg = doc_off[d], end = doc_off[d + 1];
+        if (g < 0 || g >= G) {
+            if (threadIdx.x == 0) atomicOr(bad, 1);
             continue;
         }
-        const int32_t q = g * V + w;
-        gw[i] = q;
-        if (gw_count) atomicAdd(gw_count + q, 1);
+        for (int64_t i = beg + threadIdx.x; i < end; i += blockDim.x) {
+            const int32_t w = words[i];
+            if (w < 0 || w >= V) {
+                atomicOr(bad, 2);
+                gw[i] = 0;
+                continue;
+            }
+            const int32_t q = g * V + w;
+            gw[i] = q;
+            if (gw_count) atomicAdd(gw_count + q, 1);
+        }
     }
 }
 
@@ -434,8 +436,8 @@ hipError_t launch_make_gw(const Model &m, int32_t D, const int32_t *words, const
                           hipStream_t st)
 {
     if (D <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_make_gw, dim3((unsigned)D), dim3(kBlock), 0, st, D, m.V, m.G, words,
-                       doc_off, doc_group, gw, gw_count, bad);
+    hipLaunchKernelGGL(k_make_gw, dim3((unsigned)std::min(D, kGwBlocks)), dim3(kBlock), 0, st, D,
+                       m.V, m.G, words, doc_off, doc_group, gw, gw_count, bad);
     return hipGetLastError();
 }
 

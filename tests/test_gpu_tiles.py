@@ -12,6 +12,10 @@
   (subnormal or infinite, for topics and groups without customers) or lie at
   the ends of the range where one is used; the same tolerances, and a few
   subnormal units (8 x 5e-324) where the values themselves are subnormal.
+* A fold-in of more test documents than 256-thread blocks fit one launch (2^24),
+  nearly all of them empty, against the fold-in of the others alone: a token's
+  draws depend on its index, which is the same in both, and an empty document
+  adds 0, so topics and sums are equal.
 """
 import numpy as np
 import pytest
@@ -78,4 +82,27 @@ def test_estimates_with_extreme_divisors(b, gamma, S):
     assert np.array_equal(np.isnan(p0), np.isnan(p0_o.T))
     np.testing.assert_allclose(p0, p0_o.T, rtol=1e-13, atol=4e-323)
     np.testing.assert_allclose(pg, pg_o.transpose(0, 2, 1), rtol=1e-12, atol=4e-323)
+    s.close()
+
+
+def test_foldin_of_more_documents_than_blocks_of_a_launch():
+    D = (1 << 24) + 77
+    print(f"fold-in of {D} documents", flush=True)
+    cp = _corpus(1001, 5, 9)
+    s, _ = parity.make_pair(cp, synth.workload(0), K=5)
+    rng = np.random.default_rng(1)
+    # the first and the last document, those on both sides of 2^20 and 2^24, and some others
+    at = np.unique(np.concatenate([[0, (1 << 20) - 1, 1 << 20, (1 << 24) - 1, 1 << 24, D - 1],
+                                   rng.integers(0, D, 60)]))
+    lens = rng.integers(1, 80, at.size)
+    words = rng.integers(0, cp.vocab, lens.sum()).astype(np.int32)
+    group = rng.integers(0, 3, at.size).astype(np.int32)
+    small = s.heldout(words, np.concatenate([[0], np.cumsum(lens)]), group, 3, 7)
+    full = np.zeros(D, np.int64)
+    full[at] = lens
+    group_of = np.zeros(D, np.int32)
+    group_of[at] = group
+    got = s.heldout(words, np.concatenate([[0], np.cumsum(full)]), group_of, 3, 7)
+    assert got[:2] == small[:2]
+    assert np.array_equal(got[2], small[2])
     s.close()
