@@ -559,7 +559,9 @@ struct RowWave {
             }
             if (!drew) s1 = sole_slot64(A, q, k0, s0, fabsf(__uint_as_float(t.z)));
         }
-        if (total < 0.0f) {  // decided in fp64 at the token
+        // decided in fp64 at the token (a token that keeps its topic may have no
+        // entry of its own in res: none is written where no prefix passes its target)
+        if (drew && total < 0.0f) {
             const int32_t o = (int32_t)(-1.0f - total);
             r1 = o & 1;
             s1 = o >> 1;

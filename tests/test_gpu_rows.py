@@ -6,6 +6,10 @@ small-corpus tests elsewhere reach the 32- and 64-lane instances at every
 topic count; these corpora have enough documents for the 16-lane ones, with
 lengths around whole chunks, empty documents, and (K = 520) a lane layout with
 a remainder at 64 lanes.  The bounds are the parity protocol's.
+
+Hyperparameters whose fp32 weights overflow, underflow or are no numbers: every
+draw is then decided in fp64, where they still are, so the states (and sources)
+are the oracle's.
 """
 import numpy as np
 import pytest
@@ -61,3 +65,28 @@ def test_sweeps_with_associations_match_oracle(docs, K, S):
         assert rep.mismatches == 0
     s.check()
     s.close()
+
+
+@pytest.mark.parametrize("S", [0, 3])
+@pytest.mark.parametrize("alpha,b,gamma", [(0.1, 20.0, 0.01), (1e38, 20.0, 0.01),
+                                           (1e300, 20.0, 0.01), (1e-310, 20.0, 0.01),
+                                           (0.1, 1e-40, 0.01), (0.1, 1e300, 0.01),
+                                           (0.1, 20.0, 1e-40), (0.1, 20.0, 1e300)])
+def test_sweeps_where_single_precision_does_not_reach(alpha, b, gamma, S):
+    print(f"weight rows: alpha={alpha} b={b} gamma={gamma} sources={S}", flush=True)
+    wl = synth.workload(0)
+    wl = type(wl)(**{**wl.__dict__, "alpha": alpha, "b": b, "gamma": gamma})
+    for K in (10, 20, 140):  # 16, 32 and 64 lanes
+        cp = _corpus(450, K, K)
+        assoc = synth.associations(3, cp.vocab, S, 0.3, 5) if S else None
+        s, m = parity.make_pair(cp, wl, K=K, assoc=assoc)
+        for sweep in range(3):
+            st = [x.copy() for x in parity.state_of(s, m)]
+            c = m.rebuild(*st)
+            m.sample_docs(c, *st, sweep, 7)
+            m.repair(*st, m.rebuild(*st))
+            s.sweep(sweep, 7)
+            for got, want in zip(parity.state_of(s, m), st):
+                assert np.array_equal(got, want), (K, sweep)
+        s.check()
+        s.close()
