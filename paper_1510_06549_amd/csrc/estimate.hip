@@ -114,20 +114,15 @@ __global__ void __launch_bounds__(64) k_theta(int32_t D, int32_t K, double alpha
     }
 }
 
-// 1 / d (correctly rounded) for div_by, or 0 where that reciprocal does not
-// serve: it overflows for a subnormal d (a tiny b or gamma with no customer) and
-// is 0 for an infinite one.  The line leaves the quotient and its remainder room.
-__device__ __forceinline__ double reciprocal(double d)
-{
-    return d >= 0x1p-900 && d <= 0x1p900 ? 1.0 / d : 0.0;
-}
-
-// x / d with r = reciprocal(d): the quotient by r, then one correction with the
-// exact remainder, which rounds as the division does (Markstein, "Computation of
-// elementary functions on the IBM RISC System/6000 processor", 1990).
+// x / d with r = 1 / d (correctly rounded): the quotient by r, then one
+// correction with the exact remainder, which rounds as the division does
+// (Markstein, "Computation of elementary functions on the IBM RISC System/6000
+// processor", 1990).  RECIP is false where a divisor may have no reciprocal to
+// correct: see launch_phi.
+template <bool RECIP>
 __device__ __forceinline__ double div_by(double x, double d, double r)
 {
-    if (r == 0.0) return x / d;
+    if constexpr (!RECIP) return x / d;
     const double q = x * r;
     return __fma_rn(__fma_rn(-q, d, x), r, q);
 }
@@ -152,19 +147,19 @@ struct PhiArgs {
 // 33 us and 389 us when every
 // value took three divisions and a 64-bit division of its index.
 constexpr int kPhiWords = 8, kPhiBlock = 1024;
-template <bool ASSOC>
+template <bool ASSOC, bool RECIP>
 __global__ void __launch_bounds__(kPhiBlock) k_phi(PhiArgs A)
 {
     const int32_t k = blockIdx.y * blockDim.x + threadIdx.x;
     if (k >= A.K) return;
     const int32_t g = A.g_begin + (int32_t)blockIdx.z;
-    const double d0 = A.Vgamma + (double)A.Bk[k], r0 = reciprocal(d0);
+    const double d0 = A.Vgamma + (double)A.Bk[k], r0 = 1.0 / d0;
     double dg = 1.0, wg = 0.0;
     if (A.phi) {
         dg = A.b + (double)A.Ngk[(int64_t)g * A.Kp + k];
         wg = A.b + A.a * (double)A.Tgk[(int64_t)g * A.Kp + k];
     }
-    const double rg = reciprocal(dg);
+    const double rg = 1.0 / dg;
     const bool first = A.phi0 != nullptr && blockIdx.z == 0;
     double *out = A.phi ? A.phi + (int64_t)blockIdx.z * A.V * A.K : nullptr;
     // kPhiWords consecutive words per thread, their loads together (words past
@@ -196,7 +191,7 @@ __global__ void __launch_bounds__(kPhiBlock) k_phi(PhiArgs A)
 #pragma unroll
     for (int i = 0; i < kPhiWords; ++i) {
         if (i >= nw) break;
-        double p0 = div_by(A.gamma + (double)bw[i], d0, r0);
+        double p0 = div_by<RECIP>(A.gamma + (double)bw[i], d0, r0);
         if (first) p_out[i * A.K] = p0;
         if (!A.phi) continue;
         const int32_t c =
@@ -211,10 +206,10 @@ __global__ void __launch_bounds__(kPhiBlock) k_phi(PhiArgs A)
                 const double pv = A.p64[q * A.Sp + s];
                 const int64_t v = A.srcrec[q * 2 * A.Sp + s];
                 if (pv > 0.0)
-                    p0 += pv * div_by(A.gamma + (double)A.B[v * A.Kp + k], d0, r0);
+                    p0 += pv * div_by<RECIP>(A.gamma + (double)A.B[v * A.Kp + k], d0, r0);
             }
         }
-        out[i * A.K] = div_by(n - A.a * t + wg * p0, dg, rg);
+        out[i * A.K] = div_by<RECIP>(n - A.a * t + wg * p0, dg, rg);
     }
 }
 
@@ -507,11 +502,20 @@ hipError_t launch_phi(const Model &m, const DeviceBuffers &b, int32_t g_begin, i
         if (c * x * ((y * x + 63) / 64) >= y * x * ((c * x + 63) / 64)) y = c;
     const int64_t nb = (m.V + kPhiWords * (int64_t)y - 1) / (kPhiWords * (int64_t)y);
     const dim3 block(x, y);
+    // every divisor is b or V gamma and a count below 2^31; a reciprocal that
+    // overflows (a subnormal b or V gamma, no customers) or is 0 (an infinite
+    // V gamma) has no correction, and the line leaves the remainder room
+    auto in_range = [](double d) { return d >= 0x1p-900 && d <= 0x1p900; };
+    const bool recip = in_range(A.b) && in_range(A.Vgamma);
     do {  // (a grid holds at most 65 535 groups)
         const int32_t groups = A.phi ? (g_end - A.g_begin < 32768 ? g_end - A.g_begin : 32768) : 1;
         const dim3 grid((unsigned)nb, ranges, (unsigned)groups);
-        if (m.Sp > 0) hipLaunchKernelGGL(k_phi<true>, grid, block, 0, st, A);
-        else hipLaunchKernelGGL(k_phi<false>, grid, block, 0, st, A);
+        if (!recip)
+            hipLaunchKernelGGL((m.Sp > 0 ? k_phi<true, false> : k_phi<false, false>), grid, block,
+                               0, st, A);
+        else
+            hipLaunchKernelGGL((m.Sp > 0 ? k_phi<true, true> : k_phi<false, true>), grid, block, 0,
+                               st, A);
         if (!A.phi) break;
         A.phi0 = nullptr;
         A.phi += (int64_t)groups * m.V * m.K;
