@@ -107,6 +107,10 @@ typedef struct {
  * than 65535 times: counts are held in 16 bits).  The Stirling cache takes
  * about 16 (ncap + 1)^2 bytes of device memory for ncap customers of the most
  * frequent pair: 17.2 GB at 32767, 68.7 GB at 65535.
+ * A state with enough tokens per (group, word) pair also holds weight rows (up
+ * to 8 GiB) that make its sweeps faster.  Where device memory is short they are
+ * left out, or given back to a later call that needs their memory, and sweeps go
+ * on with the same results.
  * On success *out holds the new state; on error *out is NULL.
  */
 int spdp_create(const spdp_corpus *corpus, const spdp_groups *groups, int32_t K, double alpha,
@@ -395,7 +399,7 @@ int spdp_debug_poke(spdp_state *s, int32_t g, int32_t w, int32_t k, int32_t dn, 
  * Shape of the state: out[0] = N, [1] = D, [2] = V, [3] = G, [4] = K,
  * [5] = row stride of the count arrays (topics, >= K), [6] = largest
  * per-(group, word) token count (the Stirling rows needed), [7] = device bytes
- * held.  Errors: E_ARG.
+ * held (less once the weight rows are given back).  Errors: E_ARG.
  */
 int spdp_info(const spdp_state *s, int64_t *out8);
 

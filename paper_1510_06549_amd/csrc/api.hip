@@ -63,9 +63,41 @@ struct spdp_state {
     bool timing = false;
     std::vector<EventPair> events[SPDP_NKERNELS];
     std::vector<void *> allocs;
+    // where memory is short, the weight rows and what only their sampler reads
+    // in an allocation of their own: the state samples from its count rows
+    // without them
+    void *weight_rows = nullptr;
+    int64_t weight_bytes = 0;
 };
 
 namespace {
+
+// Without the weight rows a state samples from its count rows, so they are
+// given back, where they can be, before an allocation that an entry point needs
+// is refused.
+void drop_weight_rows(spdp_state *s)
+{
+    s->m.rows = RowShape{};
+    s->b.pw = s->b.rho = nullptr;
+    s->b.fz = nullptr;
+    s->b.order_len = nullptr;
+    if (!s->weight_rows) return;
+    (void)hipStreamSynchronize(s->st);
+    (void)hipFree(s->weight_rows);
+    s->weight_rows = nullptr;
+    s->bytes -= s->weight_bytes;
+}
+
+// hipMalloc for a call on state s.
+template <typename T>
+hipError_t work_malloc(const spdp_state *s, T **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess || !s->weight_rows) return e;
+    (void)hipGetLastError();
+    drop_weight_rows(const_cast<spdp_state *>(s));  // (no output of the state changes)
+    return hipMalloc(p, bytes);
+}
 
 template <typename T>
 int dev_alloc(spdp_state *s, T **p, int64_t count, const char *what)
@@ -74,7 +106,7 @@ int dev_alloc(spdp_state *s, T **p, int64_t count, const char *what)
     if (count <= 0) count = 1;
     const size_t bytes = (size_t)count * sizeof(T);
     void *q = nullptr;
-    hipError_t e = hipMalloc(&q, bytes);
+    hipError_t e = work_malloc(s, &q, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SPDP_E_NOMEM, "hipMalloc of %zu bytes for %s failed: %s", bytes, what,
@@ -99,13 +131,17 @@ public:
         parts_[n_++] = {reinterpret_cast<void **>(p), total_};
         total_ += ((size_t)count * sizeof(T) + 255) / 256 * 256;
     }
+    size_t bytes() const { return total_; }
+    void place(void *base) const
+    {
+        for (int i = 0; i < n_; ++i) *parts_[i].p = static_cast<char *>(base) + parts_[i].at;
+    }
     int alloc(spdp_state *s, const char *what)
     {
         char *base = nullptr;
         const int rc = dev_alloc(s, &base, (int64_t)total_, what);
-        if (rc != SPDP_OK) return rc;
-        for (int i = 0; i < n_; ++i) *parts_[i].p = base + parts_[i].at;
-        return SPDP_OK;
+        if (rc == SPDP_OK) place(base);
+        return rc;
     }
 
 private:
@@ -113,10 +149,52 @@ private:
         void **p;
         size_t at;
     };
-    Part parts_[24] = {};  // the largest list has 23 arrays
+    Part parts_[24] = {};  // the largest list has 19 arrays
     int n_ = 0;
     size_t total_ = 0;
 };
+
+// Allocates the arrays of `a` and, if the model has them, the weight rows.  Both
+// together where as much memory again stays free (a second hipMalloc and
+// hipFree cost 0.3 ms of the 2.4 ms that a state of 3 million tokens takes from
+// creation to release); with less, the weight rows apart, so that they can be
+// given back, or not at all.
+int alloc_counts(spdp_state *s, const Arrays &a, const char *what)
+{
+    DeviceBuffers &B = s->b;
+    const Model &m = s->m;
+    const int64_t entries = (int64_t)m.G * m.V * m.rows.Kw;
+    Arrays w;
+    if (entries > 0) {
+        w.add(&B.pw, entries);
+        w.add(&B.rho, entries);
+        w.add(&B.fz, 2 * (int64_t)m.G * m.Kp);
+        w.add(&B.order_len, m.D);
+    }
+    const size_t need = a.bytes() + w.bytes();
+    size_t free = 0, total = 0;
+    if (entries > 0 && (hipMemGetInfo(&free, &total) != hipSuccess || free / 2 < need)) {
+        (void)hipGetLastError();
+        free = 0;
+    }
+    const bool together = free > 0;
+    char *base = nullptr;
+    const int rc = dev_alloc(s, &base, (int64_t)(together ? need : a.bytes()), what);
+    if (rc != SPDP_OK) return rc;
+    a.place(base);
+    if (together) w.place(base + a.bytes());
+    if (together || entries == 0) return SPDP_OK;
+    if (hipMalloc(&s->weight_rows, w.bytes()) != hipSuccess) {
+        (void)hipGetLastError();
+        s->weight_rows = nullptr;
+        drop_weight_rows(s);
+        return SPDP_OK;
+    }
+    w.place(s->weight_rows);
+    s->weight_bytes = (int64_t)w.bytes();
+    s->bytes += s->weight_bytes;
+    return SPDP_OK;
+}
 
 void free_state(spdp_state *s)
 {
@@ -125,6 +203,7 @@ void free_state(spdp_state *s)
     if (s->st) (void)hipStreamSynchronize(s->st);
     else (void)hipDeviceSynchronize();
     for (void *p : s->allocs) (void)hipFree(p);
+    if (s->weight_rows) (void)hipFree(s->weight_rows);
     if (s->b.zr_dbg) (void)hipFree(s->b.zr_dbg);
     if (s->b.tr_w) (void)hipFree(s->b.tr_w);
     if (s->b.tr_u) (void)hipFree(s->b.tr_u);
@@ -513,13 +592,7 @@ int create_state(const spdp_corpus *corpus, const spdp_groups *groups, const spd
         a.add(&B.part, stat_partials_needed());
         a.add(&B.exact, 1);
         a.add(&B.partial, B.partial_len);
-        if (m.rows.Kw > 0) {
-            a.add(&B.pw, rows * m.rows.Kw);
-            a.add(&B.rho, rows * m.rows.Kw);
-            a.add(&B.fz, 2 * gk);
-            a.add(&B.order_len, D);
-        }
-        TRY(a.alloc(s, "the count state and its tables"));
+        TRY(alloc_counts(s, a, "the count state and its tables"));
     }
     TRY_HIP(launch_stirling(m, B.logS, B.Q, B.Q64, B.lfact, s->st));
     TRY_HIP(launch_lgamma_table(m, B.lgt, s->st));
@@ -606,7 +679,13 @@ int spdp_sweep_async(spdp_state *s, uint32_t sweep, uint64_t seed, int32_t waves
         if ((rc = dev_alloc(s, &b.tok_doc, m.N, "token documents")) != SPDP_OK) return rc;
         if ((rc = dev_alloc(s, &b.cdk, (int64_t)m.D * m.Kp, "document counts")) != SPDP_OK)
             return rc;
-        HIP_TRY(build_visit_order(m, b, s->st));
+        hipError_t e = build_visit_order(m, b, s->st);  // (allocates what it works in)
+        if (e == hipErrorOutOfMemory && s->weight_rows) {
+            (void)hipGetLastError();
+            drop_weight_rows(s);
+            e = build_visit_order(m, b, s->st);
+        }
+        HIP_TRY(e);
     }
     if (waves == 0) {
         int cus = 0;
@@ -651,8 +730,8 @@ int spdp_counts(const spdp_state *s, int32_t g_begin, int32_t g_end, int32_t *n_
     int32_t *stage_n = nullptr, *stage_t = nullptr;
     if (where == 0) {
         // one group at a time through device staging buffers
-        HIP_TRY(hipMalloc(&stage_n, (size_t)cells * 4));
-        hipError_t e = hipMalloc(&stage_t, (size_t)cells * 4);
+        HIP_TRY(work_malloc(s, &stage_n, (size_t)cells * 4));
+        hipError_t e = work_malloc(s, &stage_t, (size_t)cells * 4);
         if (e != hipSuccess) {
             (void)hipFree(stage_n);
             HIP_TRY(e);
@@ -725,7 +804,7 @@ int spdp_estimates(spdp_state *s, int32_t g_begin, int32_t g_end, double *theta,
         int64_t need = 0;
         if (theta) need = dk;
         if ((phi0 || phi) && vk > need) need = vk;
-        if (need > 0) HIP_TRY(hipMalloc(&stage, (size_t)need * sizeof(double)));
+        if (need > 0) HIP_TRY(work_malloc(s, &stage, (size_t)need * sizeof(double)));
     }
     hipError_t e = hipSuccess;
     auto out = [&](double *dst, int64_t n, auto &&launch) {
@@ -779,7 +858,7 @@ int spdp_heldout(spdp_state *s, const spdp_corpus *test, const spdp_groups *test
     // one allocation: document sums, offsets and groups, rows, topics
     char *all = nullptr;
     const size_t nn = (size_t)(N > 0 ? N : 1), nd = (size_t)D + 1;
-    HIP_TRY(hipMalloc(&all, nd * (8 + 8 + 4) + nn * (4 + 4)));
+    HIP_TRY(work_malloc(s, &all, nd * (8 + 8 + 4) + nn * (4 + 4)));
     double *ll_d = reinterpret_cast<double *>(all);
     int64_t *off_d = reinterpret_cast<int64_t *>(ll_d + nd);
     int32_t *grp_d = reinterpret_cast<int32_t *>(off_d + nd);
@@ -837,7 +916,7 @@ int spdp_hellinger(spdp_state *s, const double *p, int32_t kp, const double *q, 
     hipError_t e = hipSuccess;
     auto dalloc = [&](int64_t n) -> double * {
         void *x = nullptr;
-        if (e == hipSuccess) e = hipMalloc(&x, (size_t)(n > 0 ? n : 1) * sizeof(double));
+        if (e == hipSuccess) e = work_malloc(s, &x, (size_t)(n > 0 ? n : 1) * sizeof(double));
         if (e != hipSuccess) return nullptr;
         tmp.push_back(x);
         return (double *)x;
@@ -933,8 +1012,8 @@ int spdp_get_assignments(const spdp_state *s, int32_t *z, uint8_t *r, int where)
     }
     int32_t *zd = nullptr;
     uint8_t *rd = nullptr;
-    HIP_TRY(hipMalloc(&zd, (size_t)m.N * sizeof(int32_t)));
-    hipError_t e = hipMalloc(&rd, (size_t)m.N);
+    HIP_TRY(work_malloc(s, &zd, (size_t)m.N * sizeof(int32_t)));
+    hipError_t e = work_malloc(s, &rd, (size_t)m.N);
     if (e == hipSuccess) e = launch_unpack_zr(m, s->b.zr[s->cur], zd, rd, s->st);
     if (e == hipSuccess && z) e = hipMemcpyAsync(z, zd, (size_t)m.N * 4, hipMemcpyDeviceToHost, s->st);
     if (e == hipSuccess && r) e = hipMemcpyAsync(r, rd, (size_t)m.N, hipMemcpyDeviceToHost, s->st);
@@ -966,9 +1045,9 @@ int set_state(spdp_state *s, const int32_t *z, const uint8_t *r, const uint8_t *
             if (st8) (void)hipFree(st8);
         };
         if (where == 0) {
-            hipError_t e = hipMalloc(&zt, (size_t)m.N * sizeof(int32_t));
-            if (e == hipSuccess) e = hipMalloc(&rt, (size_t)m.N);
-            if (e == hipSuccess && sl) e = hipMalloc(&st8, (size_t)m.N);
+            hipError_t e = work_malloc(s, &zt, (size_t)m.N * sizeof(int32_t));
+            if (e == hipSuccess) e = work_malloc(s, &rt, (size_t)m.N);
+            if (e == hipSuccess && sl) e = work_malloc(s, &st8, (size_t)m.N);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(zt, z, (size_t)m.N * 4, hipMemcpyHostToDevice, s->st);
             if (e == hipSuccess) e = hipMemcpyAsync(rt, r, (size_t)m.N, hipMemcpyHostToDevice, s->st);
@@ -1030,7 +1109,7 @@ int spdp_get_slots(const spdp_state *s, uint8_t *slot, int where)
         return sync(s);
     }
     uint8_t *sd = nullptr;
-    HIP_TRY(hipMalloc(&sd, (size_t)m.N));
+    HIP_TRY(work_malloc(s, &sd, (size_t)m.N));
     hipError_t e = launch_unpack_slot(m, s->b.zr[s->cur], sd, s->st);
     if (e == hipSuccess) e = hipMemcpyAsync(slot, sd, (size_t)m.N, hipMemcpyDeviceToHost, s->st);
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);
@@ -1063,7 +1142,7 @@ int spdp_debug_conditionals(spdp_state *s, uint32_t sweep, uint64_t seed, int64_
     const int64_t nout = m.Sp > 0 ? (int64_t)m.K * (m.S + 1) : 2 * (int64_t)m.K;
     if (!b.zr_dbg) {
         void *p = nullptr;
-        if (hipMalloc(&p, (size_t)m.N * sizeof(int32_t)) != hipSuccess) {
+        if (work_malloc(s, &p, (size_t)m.N * sizeof(int32_t)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(SPDP_E_NOMEM, "debug state buffer");
         }
@@ -1077,12 +1156,12 @@ int spdp_debug_conditionals(spdp_state *s, uint32_t sweep, uint64_t seed, int64_
         b.tr_u = nullptr;
         b.tr_cap = 0;
         void *p = nullptr;
-        if (hipMalloc(&p, (size_t)(T * nout) * sizeof(float)) != hipSuccess) {
+        if (work_malloc(s, &p, (size_t)(T * nout) * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(SPDP_E_NOMEM, "trace buffer");
         }
         b.tr_w = (float *)p;
-        if (hipMalloc(&p, (size_t)T * sizeof(float)) != hipSuccess) {
+        if (work_malloc(s, &p, (size_t)T * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(SPDP_E_NOMEM, "trace buffer");
         }
@@ -1210,7 +1289,7 @@ int spdp_check(spdp_state *s, int64_t *bad)
     const Model &m = s->m;
     const int64_t need = 2 * (int64_t)m.G * m.Kp + m.Kp + (m.Sp > 0 ? (int64_t)m.V * m.Kp : 0);
     int32_t *scratch = nullptr;
-    if (hipMalloc(&scratch, (size_t)need * sizeof(int32_t)) != hipSuccess) {
+    if (work_malloc(s, &scratch, (size_t)need * sizeof(int32_t)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(SPDP_E_NOMEM, "check scratch of %lld ints", (long long)need);
     }

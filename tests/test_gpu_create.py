@@ -9,11 +9,14 @@
 * The row index over more than one range of the state route (2^21 row positions
   each), with most rows of a wavefront empty and rows that reach across a range's
   end: the counts after a sweep are the oracle's rebuild of its states.
+* A state whose weight rows find no room, or are given back to a call that needs
+  their memory, sweeps as one that has them.
 """
 import numpy as np
 import pytest
 
 import synth
+from paper_1510_06549_amd import spdp as sp
 from tests import parity
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +61,68 @@ def test_row_index_across_route_ranges():
         print(f"route: sweep {sw}", flush=True)
     assert s.check() == 0
     s.close()
+
+
+@pytest.mark.parametrize("S", [0, 2])
+def test_states_without_room_for_weight_rows(S):
+    import torch
+
+    print(f"weight rows without room, sources={S}", flush=True)
+    rng = np.random.default_rng(8)
+    G, V, K, N = 8, 1 << 15, 1024, 20000  # 2^18 rows: 1.6 GB of counts, 2.1 GB of weight rows
+    w = rng.integers(0, 25, N).astype(np.int32)
+    args = (w, np.arange(0, N + 1, 100), np.arange(200, dtype=np.int32) % G, G, V, K, 0.1, 0.5,
+            20.0, 0.01)
+    assoc = synth.associations(G, V, S, 0.3, 5) if S else None
+    weights = 2 * 4 * G * V * K
+
+    def base_launches(s):
+        """16-bit copies of the shadow base that a sweep made: none over weight rows."""
+        sp.spdp_kernel_timing(s.h, True)
+        s.sweep(0, 3)
+        n = sp.spdp_kernel_times(s.h)["base"][1]
+        sp.spdp_kernel_timing(s.h, False)
+        return n
+
+    full = sp.Sampler(*args, assoc=assoc)
+    held = full.info["device_bytes"]
+    assert base_launches(full) == 0
+    want = parity.state_of(full, None) + ((full.slots(),) if S else ())
+
+    def leave(room):
+        torch.cuda.empty_cache()
+        free = torch.cuda.mem_get_info()[0]
+        return torch.empty(free - room, dtype=torch.uint8, device="cuda")
+
+    def check(s):
+        got = parity.state_of(s, None) + ((s.slots(),) if S else ())
+        for a, b in zip(got, want):
+            assert np.array_equal(a, b)
+        assert s.check() == 0
+
+    # no room for them
+    ballast = [leave(held - weights // 2)]
+    s = sp.Sampler(*args, assoc=assoc)
+    assert s.info["device_bytes"] <= held - weights
+    assert base_launches(s) == 1
+    del ballast
+    check(s)
+    s.close()
+
+    # room for them, until the staging buffer of an estimate (256 MiB) needs it: what is left
+    # goes in pieces of 64 MiB, a few more than the free memory counts
+    ballast = [leave(held + (1 << 30))]
+    s = sp.Sampler(*args, assoc=assoc)
+    assert s.info["device_bytes"] > held - weights // 2
+    for _ in range(64):
+        try:
+            ballast.append(torch.empty(64 << 20, dtype=torch.uint8, device="cuda"))
+        except torch.OutOfMemoryError:
+            break
+    sp.spdp_estimates(s.h, 0, 0, None, np.empty((V, K)), None)
+    assert sp.spdp_info(s.h)["device_bytes"] <= held - weights
+    assert base_launches(s) == 1
+    del ballast
+    check(s)
+    s.close()
+    full.close()
