@@ -315,7 +315,8 @@ __device__ __forceinline__ void sample_token(const SampleArgs &A, DocWave<KPL> &
             const float hi = readlane_f(excl + s[cL], L);
             const float lo = readlane_f(cL > 0 ? excl + s[cL > 0 ? cL - 1 : 0] : excl, L);
             const float margin = fix_margin<KPL>() * total;
-            fix = (target - lo < margin) || (hi - target < margin);
+            // (written so that a target or prefix that is no number is decided there too)
+            fix = !(target - lo >= margin && hi - target >= margin);
             jstar = L * NO + cL;
         }
         if (fix) {

@@ -220,7 +220,8 @@ __global__ void __launch_bounds__(64) k_sample_async(AsyncArgs A)
             const float hi = readlane_f(excl + s[cL], L);
             const float lo = readlane_f(cL > 0 ? excl + s[cL > 0 ? cL - 1 : 0] : excl, L);
             const float margin = kAsyncMargin * total;
-            fix = (target - lo < margin) || (hi - target < margin);
+            // (written so that a target or prefix that is no number is decided there too)
+            fix = !(target - lo >= margin && hi - target >= margin);
             jstar = L * NO + cL;
         }
         if (fix) {

@@ -7,14 +7,15 @@ topic count; these corpora have enough documents for the 16-lane ones, with
 lengths around whole chunks, empty documents, and (K = 520) a lane layout with
 a remainder at 64 lanes.  The bounds are the parity protocol's.
 
-Hyperparameters whose fp32 weights overflow, underflow or are no numbers: every
-draw is then decided in fp64, where they still are, so the states (and sources)
-are the oracle's.
+Hyperparameters whose fp32 weights overflow or are no numbers, or are small but
+still normal: a draw that fp32 cannot decide is decided in fp64, so the states
+(and sources) are the oracle's.
 """
 import numpy as np
 import pytest
 
 import synth
+from paper_1510_06549_amd import spdp as sp
 from tests import parity
 
 pytestmark = pytest.mark.gpu
@@ -67,26 +68,75 @@ def test_sweeps_with_associations_match_oracle(docs, K, S):
     s.close()
 
 
+EXTREMES = [(0.1, 20.0, 0.01), (1e38, 20.0, 0.01), (1e300, 20.0, 0.01), (1e-310, 20.0, 0.01),
+            (0.1, 1e-40, 0.01), (0.1, 1e300, 0.01), (0.1, 20.0, 1e-25), (0.1, 20.0, 1e300)]
+
+
+def _extreme(alpha, b, gamma):
+    wl = synth.workload(0)
+    return type(wl)(**{**wl.__dict__, "alpha": alpha, "b": b, "gamma": gamma})
+
+
+def _sweeps_equal_oracle(s, m, sweeps):
+    for sweep in range(sweeps):
+        st = [x.copy() for x in parity.state_of(s, m)]
+        c = m.rebuild(*st)
+        m.sample_docs(c, *st, sweep, 7)
+        m.repair(*st, m.rebuild(*st))
+        s.sweep(sweep, 7)
+        for got, want in zip(parity.state_of(s, m), st):
+            assert np.array_equal(got, want), sweep
+    assert s.check() == 0
+
+
 @pytest.mark.parametrize("S", [0, 3])
-@pytest.mark.parametrize("alpha,b,gamma", [(0.1, 20.0, 0.01), (1e38, 20.0, 0.01),
-                                           (1e300, 20.0, 0.01), (1e-310, 20.0, 0.01),
-                                           (0.1, 1e-40, 0.01), (0.1, 1e300, 0.01),
-                                           (0.1, 20.0, 1e-40), (0.1, 20.0, 1e300)])
+@pytest.mark.parametrize("alpha,b,gamma", EXTREMES)
 def test_sweeps_where_single_precision_does_not_reach(alpha, b, gamma, S):
     print(f"weight rows: alpha={alpha} b={b} gamma={gamma} sources={S}", flush=True)
-    wl = synth.workload(0)
-    wl = type(wl)(**{**wl.__dict__, "alpha": alpha, "b": b, "gamma": gamma})
+    wl = _extreme(alpha, b, gamma)
     for K in (10, 20, 140):  # 16, 32 and 64 lanes
         cp = _corpus(450, K, K)
         assoc = synth.associations(3, cp.vocab, S, 0.3, 5) if S else None
         s, m = parity.make_pair(cp, wl, K=K, assoc=assoc)
-        for sweep in range(3):
-            st = [x.copy() for x in parity.state_of(s, m)]
-            c = m.rebuild(*st)
-            m.sample_docs(c, *st, sweep, 7)
-            m.repair(*st, m.rebuild(*st))
-            s.sweep(sweep, 7)
-            for got, want in zip(parity.state_of(s, m), st):
-                assert np.array_equal(got, want), (K, sweep)
-        s.check()
+        _sweeps_equal_oracle(s, m, 3)
         s.close()
+
+
+def _sparse(cp, words, seed):
+    """cp with every other token one of `words` more words, equally likely."""
+    rng = np.random.default_rng(seed)
+    w = np.where(np.arange(cp.words.size) % 2, cp.words,
+                 cp.vocab + rng.integers(0, words, cp.words.size)).astype(np.int32)
+    z = np.zeros_like(w)
+    return synth.Corpus(w, cp.doc_off, cp.doc_group, z, z.astype(np.uint8), 3, cp.vocab + words)
+
+
+@pytest.mark.parametrize("S", [0, 3])
+@pytest.mark.parametrize("alpha,b,gamma", EXTREMES)
+def test_sparse_sweeps_where_single_precision_does_not_reach(alpha, b, gamma, S):
+    """The same over count rows: too few tokens per row for weight rows."""
+    print(f"count rows: alpha={alpha} b={b} gamma={gamma} sources={S}", flush=True)
+    wl = _extreme(alpha, b, gamma)
+    for K in (60, 140):  # padding topics in a lane's slice, and lanes of them only
+        cp = _sparse(_corpus(450, K, K), 6000, 3)
+        assoc = synth.associations(3, cp.vocab, S, 0.3, 5) if S else None
+        s, m = parity.make_pair(cp, wl, K=K, assoc=assoc)
+        sp.spdp_kernel_timing(s.h, True)
+        _sweeps_equal_oracle(s, m, 3)
+        assert sp.spdp_kernel_times(s.h)["base"][1] == 3  # a 16-bit base each: over count rows
+        s.close()
+
+
+@pytest.mark.parametrize("alpha,b,gamma", EXTREMES)
+def test_asynchronous_sweeps_where_single_precision_does_not_reach(alpha, b, gamma):
+    print(f"asynchronous sweep: alpha={alpha} b={b} gamma={gamma}", flush=True)
+    cp = _corpus(450, 60, 60)
+    s, m = parity.make_pair(cp, _extreme(alpha, b, gamma), K=60)
+    z, r = s.assignments()
+    c = m.rebuild(z, r)
+    for sweep in range(2):
+        s.sweep_async(sweep, 7, waves=1, live_totals=True)
+        m.sweep(c, z, r, sweep, 7, mode="ordered", order=m.interleaved_order())
+        zg, rg = s.assignments()
+        assert np.array_equal(zg, z) and np.array_equal(rg, r), sweep
+    s.close()
