@@ -270,9 +270,15 @@ __device__ inline int32_t sole_slot64(const RowArgs &A, int32_t q, int32_t k0, i
 // sampler at the memory's latency (10 MB in flight over the chip).
 constexpr int kRowBuffers = 4;
 
-// wavefronts per SIMD that the registers are budgeted for (without scratch in
-// the token loop)
-constexpr int row_waves(int kpl) { return kpl <= 8 ? 5 : (kpl <= 13 ? 4 : 3); }
+// Wavefronts per SIMD that the registers are budgeted for: the plain instances
+// use no scratch.  With word associations those of up to four topics a lane
+// reload a few values per chunk of tokens (none per token) at five, which is
+// still faster than four without: 3 sources, 1.5 million tokens in 20 000
+// documents, K = 128: 542 us a sweep at five, 553 at four.  From five topics a lane on
+// a reload per token, which waits for the rows requested ahead as well, costs
+// more than the wavefront: K = 192 there, 764 us at five, 710 at four; plain,
+// K = 224: 414 and 396.
+constexpr int row_waves(int kpl) { return kpl <= 4 ? 5 : (kpl <= 13 ? 4 : 3); }
 
 constexpr int kTok = 16;  // tokens per chunk
 
@@ -360,8 +366,6 @@ struct RowWave {
     }
     __device__ __forceinline__ void prep1(const RowArgs &A)
     {
-        // (no token: the group's first row stands in, unused)
-        if (len == 0) s_qn = (uint32_t)gV | ((uint32_t)A.row_narrow[gV] << 31);
         const int32_t q = (int32_t)(s_qn & 0x7FFFFFFFu);
         const int32_t k0 = zr_topic(s_zr), r0 = s_zr & 1;
         s_cell = load_cell(A, q, k0, (int32_t)s_qn < 0);
@@ -475,10 +479,15 @@ struct RowWave {
         const bool near = below < margin || above < margin;
         const bool here = __builtin_amdgcn_inverse_ballot_w64(at);
         int32_t kk = keep ? jo : (here ? cnt : -1);
-        if (here)
-            res[ch & 1][grp * kTok + x] =
+        if (here) {
+            int32_t g = grp;
+            // (its address made anew where, kept over the chunk, it was one
+            // register too many and was reloaded for every token)
+            if constexpr (ASSOC || KPL > 4) asm volatile("" : "+v"(g));
+            res[ch & 1][g * kTok + x] =
                 make_uint4((uint32_t)(kbase + cnt), __float_as_uint(below),
                            __float_as_uint(below + above), __float_as_uint(total));
+        }
         const unsigned long long doubt = __ballot(near) & at & ~__ballot(keep);
         unsigned long long bad = 0;
         if (doubt != 0 || __popcll(at) != NG) {
@@ -604,12 +613,18 @@ __global__ void __launch_bounds__(64, row_waves(KPL)) k_sample_rows(RowArgs A)
         if (w.len > 0) w.beg = (int32_t)A.doc_off[d];
         g = A.doc_group[d];
     }
-    w.gV = g * A.V;
-    w.gK = g * A.Kp;
     int32_t longest = 0;
 #pragma unroll
     for (int n = 0; n < RW::NG; ++n) longest = max(longest, readlane(w.len, n * LANES));
     if (longest == 0) return;
+    // (an empty document's lanes prepare the first token of one that is not, unused)
+    const int32_t some = __ffsll((long long)__ballot(w.len > 0)) - 1;
+    if (w.len == 0) {
+        w.beg = readlane(w.beg, some);
+        g = readlane(g, some);
+    }
+    w.gV = g * A.V;
+    w.gK = g * A.Kp;
 
     // document counts
 #pragma unroll
