@@ -63,8 +63,20 @@ def test_row_index_across_route_ranges():
     s.close()
 
 
+@pytest.fixture
+def return_memory():
+    """What torch holds goes back to the device, also after a failure."""
+    import gc
+
+    import torch
+
+    yield
+    gc.collect()
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("S", [0, 2])
-def test_states_without_room_for_weight_rows(S):
+def test_states_without_room_for_weight_rows(S, return_memory):
     import torch
 
     print(f"weight rows without room, sources={S}", flush=True)
