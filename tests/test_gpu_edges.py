@@ -108,9 +108,46 @@ def test_invalid_arguments():
         sp.spdp_create(words, off, np.array([1], np.int32), 1, 3, 4, 0.1, 0.5, 1.0, 0.1)
 
 
+# What a sweep's sampling step reads is decided when the state is created: weight
+# rows where 24 N >= K times the rows that have tokens, count rows below.  The
+# debug trace always reads count rows, in instances of its own.
+
+
+def base_copies(s, sweep, seed):
+    """16-bit copies of the shadow base that a sweep makes: 1 over count rows, 0
+    over weight rows (the sweep is run)."""
+    from paper_1510_06549_amd import spdp as sp
+
+    sp.spdp_kernel_timing(s.h, True)
+    s.sweep(sweep, seed)
+    n = sp.spdp_kernel_times(s.h)["base"][1]
+    sp.spdp_kernel_timing(s.h, False)
+    return n
+
+
+@pytest.mark.parametrize("sources", [0, 2])
+@pytest.mark.parametrize("more", [0, 1])
+def test_weight_rows_or_count_rows(more, sources):
+    """One state on either side of the line: 48 rows of K = 60 topics that have
+    tokens take 120 tokens to be sampled over weight rows, and 119 over count
+    rows; with one more token there are weight rows."""
+    n = 119 + more
+    say(f"{n} tokens in 48 rows, K = 60, sources {sources}")
+    docs = [(0, [w % 24 for w in range(60)]), (1, [w % 24 for w in range(n - 60)])]
+    cp = corpus_from_docs(docs, vocab=30)  # (six words without tokens)
+    assert len(np.unique(cp.words + 30 * np.repeat(cp.doc_group, np.diff(cp.doc_off)))) == 48
+    assoc = synth.associations(2, 30, sources, 0.3, 5) if sources else None
+    s, m = parity.make_pair(cp, W(K=60), assoc=assoc)
+    for sw in range(3):
+        parity.one_step(s, m, sw, 3)
+    assert base_copies(s, 3, 3) == 1 - more
+    s.close()
+
+
 def test_shadow_base_counts_beyond_16_bits():
-    """A shadow-base count above 65535 (the sampler's 32-bit launch then
-    reads B itself where the 16-bit copy saturates): 4 groups each with 16400
+    """A shadow-base count above 65535 (the traced sampler's 32-bit launch then
+    reads B itself where the 16-bit copy saturates; the sweep is over weight
+    rows, which are made from B): 4 groups each with 16400
     occurrences of word 0, all seated at their own table of topic 0, give
     B[0][0] = 65600."""
     say("shadow-base count beyond 16 bits")
@@ -139,28 +176,44 @@ def test_shadow_base_beyond_16_bits_with_many_documents():
     documents, more than the workgroups of that launch's persistent grid, so
     that workgroups claim several documents each: 4 groups of 1 250 documents,
     14 occurrences of word 0 in each, all seated at their own table of topic 0
-    (B[0][0] = 70 000), and 6 other tokens per document at random states."""
+    (B[0][0] = 70 000), and 6 other tokens per document at random states.  The
+    trace runs that launch; the sweep, over weight rows, reads B."""
     say("shadow-base count beyond 16 bits, K = 500, 5000 documents")
     wide_base_case(None)
 
 
+@pytest.mark.parametrize("sources", [None, 4])
+def test_sweeps_over_count_rows_with_shadow_base_beyond_16_bits(sources):
+    """The same counts where the sweep itself samples from count rows: the other
+    tokens of every document are of words that occur once in their group, so
+    that 7 504 rows share 77 500 tokens."""
+    say(f"shadow-base count beyond 16 bits, count rows, K = 500, sources {sources}")
+    wide_base_case(sources, sparse=True)
+
+
 def test_shadow_base_beyond_16_bits_with_word_associations():
-    """The association sampler's 32-bit shadow-base launch in the instance the
-    benchmark runs (K = 500, four sources per word), over more documents than
-    its persistent grid has workgroups: the corpus of the test above, every
+    """The association sampler's 32-bit shadow-base launch (in its trace) at
+    K = 500 and four sources per word, over more documents than
+    its persistent grid has workgroups: the corpus of the tests above, every
     table of word 0 at topic 0 drawing its first source, which is word 0
     itself, so the source-keyed count B[0][0] = 70 000."""
     say("shadow-base count beyond 16 bits, word associations, K = 500")
     wide_base_case(4)
 
 
-def wide_base_case(sources):
+def wide_base_case(sources, sparse=False):
     rng = np.random.default_rng(11)
     V, K = 60, 500
+    if sparse:
+        V = 1 + 3 * 625
     docs = []
     for g in range(4):
-        for _ in range(1250):
-            d = [0] * 14 + list(rng.integers(1, V, size=6))
+        for i in range(1250):
+            # (sparse: three words of its own in every other document)
+            other = rng.integers(1, V, size=6)
+            if sparse:
+                other = 1 + 3 * (i // 2) + np.arange(3 if i % 2 else 0)
+            d = [0] * 14 + list(other)
             rng.shuffle(d)
             docs.append((g, d))
     cp = corpus_from_docs(docs, vocab=V)
@@ -180,6 +233,7 @@ def wide_base_case(sources):
         rep, ch, rp = parity.one_step(s, m, sw, 23)
         say(f"  sweep {sw}: {rep}")
     assert s.check() == 0
+    assert base_copies(s, 2, 23) == (1 if sparse else 0)
     s.close()
 
 
@@ -250,8 +304,9 @@ def test_stirling_cache_above_23k_customers():
 
 def test_stirling_cache_past_2_29_ratio_pairs():
     """A (group, word) pair with 33 000 tokens: 544 M ratio pairs, past the 2^29
-    that 32-bit byte offsets reach, so the samplers' 64-bit-address instance
-    runs (17.4 GB of tables).  Weights, draws and the rebuild match the oracle
+    that 32-bit byte offsets reach, so the traced samplers' 64-bit-address
+    instance runs (17.4 GB of tables; the sweep is over weight rows).  Weights,
+    draws and the rebuild match the oracle
     over two sweeps; a pair with 65 536 tokens, which 16-bit counts cannot
     hold, is refused with E_RANGE."""
     from paper_1510_06549_amd import spdp as sp
@@ -266,28 +321,38 @@ def test_stirling_cache_past_2_29_ratio_pairs():
 
 
 def test_stirling_cache_past_2_29_ratio_pairs_with_word_associations():
-    """The association sampler's 64-bit-address instance: the same 33 000-token
+    """The association sampler's 64-bit-address instance (traced): the same 33 000-token
     pair under P = 0.7 I + 0.3 Pi (two sources in every row: word 0 lists
     itself and word 4), so new tables of word 0 draw either source.  Weights,
     draws, sources and the rebuild match the oracle over two sweeps."""
     check_large_pair(33000, 18, sources=2)
 
 
-def check_large_pair(count, seed, sources=0):
+@pytest.mark.parametrize("sources", [0, 2])
+def test_sweeps_over_count_rows_past_2_29_ratio_pairs(sources):
+    """The 64-bit-address instances of the sweep itself, over count rows: the
+    same pair, 24 000 words that occur once, and K = 60."""
+    check_large_pair(33000, 19, sources, once=8000, K=60)
+
+
+def check_large_pair(count, seed, sources=0, once=0, K=3):
     say(f"Stirling cache for {count} customers" + (f", {sources} sources" if sources else ""))
     rng = np.random.default_rng(seed)
     docs = []
-    for _ in range(3):
+    V = 5 + 3 * once
+    for i in range(3):
         d = [0] * (count // 3) + list(rng.integers(1, 5, size=30))
+        d += list(5 + i * once + np.arange(once))
         rng.shuffle(d)
         docs.append((0, d))
-    cp = corpus_from_docs(docs, vocab=5)
-    wl = W(K=3, alpha=0.5, a=0.5, b=20.0, gamma=0.1)
-    assoc = synth.associations(1, 5, sources, 0.3, seed) if sources else None
+    cp = corpus_from_docs(docs, vocab=V)
+    wl = W(K=K, alpha=0.5, a=0.5, b=20.0, gamma=0.1)
+    assoc = synth.associations(1, V, sources, 0.3, seed) if sources else None
     s, m = parity.make_pair(cp, wl, assoc=assoc)
     assert s.info["ncap"] == count and s.S == sources
     for sw in range(2):
         rep, _, _ = parity.one_step(s, m, sw, 29)
         say(f"  sweep {sw}: {rep}")
     assert s.check() == 0
+    assert base_copies(s, 2, 29) == (1 if once else 0)
     s.close()
