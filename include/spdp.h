@@ -396,6 +396,19 @@ int spdp_check(spdp_state *s, int64_t *bad);
 int spdp_debug_poke(spdp_state *s, int32_t g, int32_t w, int32_t k, int32_t dn, int32_t dt);
 
 /*
+ * Test hook: the weight rows that the next sweep would sample over, for rows
+ * q = g V + w in [row_begin, row_end), into host arrays [rows][K]:
+ *   pw[q][k]   both outcomes' weight of topic k but for the document's factor
+ *              (alpha + c), from the state's counts with every token in them
+ *   rho[q][k]  the share of the r = 1 outcomes in it
+ * (0 for rows without tokens).  Synchronises.
+ * Errors: E_ARG (bad range, or the state samples from count rows), E_NOMEM,
+ * E_HIP.
+ */
+int spdp_debug_weight_rows(spdp_state *s, int64_t row_begin, int64_t row_end, float *pw,
+                           float *rho);
+
+/*
  * Shape of the state: out[0] = N, [1] = D, [2] = V, [3] = G, [4] = K,
  * [5] = row stride of the count arrays (topics, >= K), [6] = largest
  * per-(group, word) token count (the Stirling rows needed), [7] = device bytes

@@ -1348,6 +1348,34 @@ int spdp_debug_poke(spdp_state *s, int32_t g, int32_t w, int32_t k, int32_t dn, 
     return sync(s);
 }
 
+int spdp_debug_weight_rows(spdp_state *s, int64_t row_begin, int64_t row_end, float *pw,
+                           float *rho)
+{
+    if (!s || !pw || !rho) return fail(SPDP_E_ARG, "null argument");
+    const Model &m = s->m;
+    if (row_begin < 0 || row_end < row_begin || row_end > (int64_t)m.G * m.V)
+        return fail(SPDP_E_ARG, "bad row range");
+    if (m.rows.Kw == 0) return fail(SPDP_E_ARG, "the state has no weight rows");
+    HIP_TRY(hipSetDevice(s->device));
+    const size_t bytes = (size_t)((row_end - row_begin) * m.K) * sizeof(float);
+    if (bytes == 0) return SPDP_OK;
+    char *stage = nullptr;
+    if (hipMalloc(&stage, 2 * bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(SPDP_E_NOMEM, "staging buffer of %zu bytes", 2 * bytes);
+    }
+    float *w = reinterpret_cast<float *>(stage), *r = reinterpret_cast<float *>(stage + bytes);
+    hipError_t e = launch_weights(m, s->b, s->st);
+    if (e == hipSuccess)
+        e = launch_weight_topics(m, s->b, row_begin, row_end - row_begin, w, r, s->st);
+    if (e == hipSuccess) e = hipMemcpyAsync(pw, w, bytes, hipMemcpyDeviceToHost, s->st);
+    if (e == hipSuccess) e = hipMemcpyAsync(rho, r, bytes, hipMemcpyDeviceToHost, s->st);
+    if (e == hipSuccess) e = hipStreamSynchronize(s->st);
+    (void)hipFree(stage);
+    HIP_TRY(e);
+    return SPDP_OK;
+}
+
 int spdp_info(const spdp_state *s, int64_t *out8)
 {
     if (!s || !out8) return fail(SPDP_E_ARG, "null argument");

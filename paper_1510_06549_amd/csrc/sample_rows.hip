@@ -177,6 +177,28 @@ __global__ void __launch_bounds__(kWindow / 2) k_doc_order(int32_t D, int32_t do
         order[beg + i] = (int32_t)(beg + (int64_t)(uint32_t)key[i]);
 }
 
+// Test hook: the weights and shares of n rows topic by topic ([n][K]; 0 for a
+// row without tokens), from the layout of row_pos.
+__global__ void k_weight_topics(int64_t n, int32_t K, int32_t Kw, int32_t lanes, int32_t kpl,
+                                const int32_t *__restrict__ row_off,
+                                const float *__restrict__ pw, const float *__restrict__ rho,
+                                float *__restrict__ pw_out, float *__restrict__ rho_out)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n * K) return;
+    const int64_t q = i / K;
+    const int32_t k = (int32_t)(i - q * K), l = k / kpl, j = k % kpl, c = j >> 2;
+    const int32_t at = c < (kpl >> 2) ? (c * lanes + l) * 4 + (j & 3)
+                                      : (kpl >> 2) * lanes * 4 + l * (kpl & 3) + (j & 3);
+    const bool used = row_off[q] < row_off[q + 1];
+    pw_out[i] = used ? pw[q * Kw + at] : 0.0f;
+    rho_out[i] = used ? rho[q * Kw + at] : 0.0f;
+}
+
+// Topics per lane of the kernel's instances: every number up to 8, where a topic
+// more is the largest share of a token's work, then 10, 12, 13, 14 and 16: a lane of
+// 9, 11 or 15 takes the next, at most a ninth more than it needs (weights of 0).
+// Each number is up to six kernels of some 100 KB.
 int instance_kpl(int32_t topics)
 {
     if (topics <= 8) return topics;
@@ -263,6 +285,17 @@ hipError_t launch_weights(const Model &m, const DeviceBuffers &b, hipStream_t st
     const dim3 grid((unsigned)((A.rows + per - 1) / per)), block(units, per);
     if (m.Sp > 0) hipLaunchKernelGGL(k_weights<true>, grid, block, 0, st, A);
     else hipLaunchKernelGGL(k_weights<false>, grid, block, 0, st, A);
+    return hipGetLastError();
+}
+
+hipError_t launch_weight_topics(const Model &m, const DeviceBuffers &b, int64_t row_begin,
+                                int64_t n, float *pw, float *rho, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    const int64_t nb = (n * m.K + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_weight_topics, dim3((unsigned)nb), dim3(kBlock), 0, st, n, m.K, m.rows.Kw,
+                       m.rows.lanes, m.rows.kpl, b.row_off + row_begin,
+                       b.pw + row_begin * m.rows.Kw, b.rho + row_begin * m.rows.Kw, pw, rho);
     return hipGetLastError();
 }
 

@@ -294,6 +294,8 @@ RowShape row_shape(int64_t N, int32_t D, int64_t rows, int64_t rows_used, int32_
 hipError_t launch_doc_order(const Model &m, const int64_t *doc_off, int32_t *order,
                             hipStream_t st);
 hipError_t launch_weights(const Model &m, const DeviceBuffers &b, hipStream_t st);
+hipError_t launch_weight_topics(const Model &m, const DeviceBuffers &b, int64_t row_begin,
+                                int64_t n, float *pw, float *rho, hipStream_t st);
 hipError_t launch_sample_rows(const Model &m, const DeviceBuffers &b, const int32_t *zr_old,
                               int32_t *zr_new, uint32_t sweep, uint64_t seed, hipStream_t st);
 hipError_t launch_loglik(const Model &m, const DeviceBuffers &b, const int32_t *zr,

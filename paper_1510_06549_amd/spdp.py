@@ -34,7 +34,7 @@ EXPORTS = (
     "spdp_estimates", "spdp_heldout", "spdp_hellinger", "spdp_align_topics",
     "spdp_create_assoc", "spdp_get_slots", "spdp_set_assignments_assoc", "spdp_max_sources",
     "spdp_sweep_async", "spdp_read_probe", "spdp_check", "spdp_debug_poke",
-    "spdp_hellinger_noalloc",
+    "spdp_hellinger_noalloc", "spdp_debug_weight_rows",
 )
 
 
@@ -131,6 +131,8 @@ def load_library() -> C.CDLL:
     L.spdp_check.restype = cint
     L.spdp_debug_poke.argtypes = [vp, i32, i32, i32, i32, i32]
     L.spdp_debug_poke.restype = cint
+    L.spdp_debug_weight_rows.argtypes = [vp, i64, i64, vp, vp]
+    L.spdp_debug_weight_rows.restype = cint
     return L
 
 
@@ -340,6 +342,11 @@ def spdp_debug_poke(h, g, w, k, dn, dt):
     _check(lib().spdp_debug_poke(h, int(g), int(w), int(k), int(dn), int(dt)))
 
 
+def spdp_debug_weight_rows(h, row_begin, row_end, pw, rho):
+    _check(lib().spdp_debug_weight_rows(h, int(row_begin), int(row_end), pw.ctypes.data,
+                                        rho.ctypes.data))
+
+
 def spdp_info(h) -> dict:
     out = np.zeros(8, dtype=np.int64)
     _check(lib().spdp_info(h, out.ctypes.data))
@@ -474,6 +481,12 @@ class Sampler:
 
     def poke(self, g, w, k, dn, dt):
         spdp_debug_poke(self.h, g, w, k, dn, dt)
+
+    def weight_rows(self):
+        """(pw, rho) [G V, K] of the weight rows, fp32."""
+        pw, rho = (np.empty((self.G * self.V, self.K), dtype=np.float32) for _ in range(2))
+        spdp_debug_weight_rows(self.h, 0, self.G * self.V, pw, rho)
+        return pw, rho
 
     def conditionals(self, sweep, seed, tok_begin, tok_end):
         T = tok_end - tok_begin
