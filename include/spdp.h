@@ -373,7 +373,8 @@ int spdp_kernel_times(spdp_state *s, double *ms, int64_t *launches);
  * every cell must satisfy 0 <= t <= n with t > 0 exactly when n > 0 (a cell
  * with customers but no table has joint probability zero).  Checked: every
  * count row (and the 16-bit copy of a narrow row), the totals N_gk, T_gk,
- * B_k, the shadow-base counts B and their 16-bit copy and width flag, and
+ * B_k, the shadow-base counts B (where the state has made them, for sampling
+ * from count rows, also their 16-bit copy and width flag), and
  * every token's topic and source slot.  The read-only counterpart of the
  * count regeneration the thesis runs on the host after a parallel iteration
  * (Algorithm MGPU-DP-SPDP Host).  *bad (may be NULL) receives the number of

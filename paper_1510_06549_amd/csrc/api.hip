@@ -270,7 +270,7 @@ hipError_t widen_rows(const spdp_state *s)
 }
 
 // The 16-bit copy of the shadow base, once after each rebuild, for the samplers
-// over count rows and the invariant check.
+// over count rows.
 hipError_t copy_base16(spdp_state *s)
 {
     if (s->base16) return hipSuccess;
@@ -1295,8 +1295,8 @@ int spdp_check(spdp_state *s, int64_t *bad)
     }
     unsigned long long c[4] = {0, 0, 0, 0};
     hipError_t e = launch_fill_u64(s->b.ctr, 4, 0, s->st);
-    if (e == hipSuccess) e = copy_base16(s);
-    if (e == hipSuccess) e = launch_check(m, s->b, s->b.zr[s->cur], scratch, s->b.ctr, s->st);
+    if (e == hipSuccess)
+        e = launch_check(m, s->b, s->b.zr[s->cur], s->base16, scratch, s->b.ctr, s->st);
     if (e == hipSuccess) e = hipMemcpyAsync(c, s->b.ctr, sizeof c, hipMemcpyDeviceToHost, s->st);
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);
     (void)hipFree(scratch);

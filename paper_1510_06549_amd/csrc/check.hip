@@ -14,7 +14,8 @@
 //                  cells; tokens with a topic out of range or (word
 //                  associations) a head whose slot names no source
 //   k_check_base   plain model: B[w][k] = sum_g t[g][w][k] over the same
-//                  copies, B16 = min(B, 65535), and the width flag
+//                  copies; where the state has made B16, B16 = min(B, 65535)
+//                  and the width flag
 //   k_base_heads / k_cmp_base
 //                  word associations: B recounted from the heads' sources
 //   k_cmp_i32      recomputed totals against the stored ones
@@ -90,8 +91,8 @@ __global__ void __launch_bounds__(64) k_check_rows(int32_t K, int32_t Kp, int32_
     }
 }
 
-// B[w][k] against sum_g t[g][w][k] of the stored rows, B16 against min(B,
-// 65535); over counts the cells with B > 65535.
+// B[w][k] against sum_g t[g][w][k] of the stored rows, B16 (unless null) against
+// min(B, 65535); over counts the cells with B > 65535.
 __global__ void k_check_base(int32_t G, int32_t V, int32_t Kp, const int32_t *__restrict__ nt,
                              const uint16_t *__restrict__ nt16,
                              const uint8_t *__restrict__ row_narrow,
@@ -111,7 +112,7 @@ __global__ void k_check_base(int32_t G, int32_t V, int32_t Kp, const int32_t *__
         }
         const int32_t b = B[j];
         big = b > 0xFFFF;
-        wrong = b != s || B16[j] != (uint16_t)(big ? 0xFFFF : b);
+        wrong = b != s || (B16 && B16[j] != (uint16_t)(big ? 0xFFFF : b));
     }
     add_bad(bad, wrong);
     add_bad(over, big);
@@ -142,7 +143,7 @@ __global__ void k_cmp_base(int64_t cells, const int32_t *__restrict__ B,
     if (j < cells) {
         const int32_t b = B[j];
         big = b > 0xFFFF;
-        wrong = b != Bre[j] || B16[j] != (uint16_t)(big ? 0xFFFF : b);
+        wrong = b != Bre[j] || (B16 && B16[j] != (uint16_t)(big ? 0xFFFF : b));
     }
     add_bad(bad, wrong);
     add_bad(over, big);
@@ -167,10 +168,12 @@ __global__ void k_check_wide(const int32_t *__restrict__ wide,
 
 // bad[0]: row cells and token states; bad[1]: totals and shadow base;
 // bad[2]: cells with B > 65535 (scratch for the width check).  scratch holds
-// 2 G Kp + Kp ints, plus V Kp with word associations.
-hipError_t launch_check(const Model &m, const DeviceBuffers &b, const int32_t *zr,
+// 2 G Kp + Kp ints, plus V Kp with word associations.  base16: the 16-bit copy
+// of the shadow base and its width flag are in use, and checked.
+hipError_t launch_check(const Model &m, const DeviceBuffers &b, const int32_t *zr, bool base16,
                         int32_t *scratch, unsigned long long *bad, hipStream_t st)
 {
+    const uint16_t *B16 = base16 ? b.B16 : nullptr;
     const int64_t rows = (int64_t)m.G * m.V;
     const int64_t gk = (int64_t)m.G * m.Kp, vk = (int64_t)m.V * m.Kp;
     const size_t lds = (size_t)m.Kp * sizeof(int32_t);
@@ -197,13 +200,14 @@ hipError_t launch_check(const Model &m, const DeviceBuffers &b, const int32_t *z
             hipLaunchKernelGGL(k_base_heads, dim3((unsigned)blocks_for(m.N, kBlock)), dim3(kBlock),
                                0, st, m.N, m.Kp, m.Sp, b.gw, b.srcrec, zr, Bre);
         hipLaunchKernelGGL(k_cmp_base, dim3((unsigned)blocks_for(vk, kBlock)), dim3(kBlock), 0, st,
-                           vk, b.B, Bre, b.B16, bad + 1, bad + 2);
+                           vk, b.B, Bre, B16, bad + 1, bad + 2);
     } else {
         hipLaunchKernelGGL(k_check_base, dim3((unsigned)blocks_for(vk, kBlock)), dim3(kBlock), 0,
-                           st, m.G, m.V, m.Kp, b.nt, b.nt16, b.row_narrow, b.B, b.B16, bad + 1,
+                           st, m.G, m.V, m.Kp, b.nt, b.nt16, b.row_narrow, b.B, B16, bad + 1,
                            bad + 2);
     }
-    hipLaunchKernelGGL(k_check_wide, dim3(1), dim3(64), 0, st, b.wide, bad + 2, bad + 1);
+    if (base16)
+        hipLaunchKernelGGL(k_check_wide, dim3(1), dim3(64), 0, st, b.wide, bad + 2, bad + 1);
     return hipGetLastError();
 }
 

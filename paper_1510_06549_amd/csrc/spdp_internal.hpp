@@ -267,8 +267,9 @@ hipError_t launch_unpack_counts(const Model &m, const DeviceBuffers &b, int32_t 
                                 int32_t *n_out, int32_t *t_out, hipStream_t st);
 // invariant check of the count state (count rows, in the copy the rebuild
 // writes, against a recount of the tokens' states; the shadow base; the
-// totals): the number of failing cells or totals is added to *bad
-hipError_t launch_check(const Model &m, const DeviceBuffers &b, const int32_t *zr,
+// totals): the number of failing cells or totals is added to *bad; base16:
+// the 16-bit copy of the shadow base is there too
+hipError_t launch_check(const Model &m, const DeviceBuffers &b, const int32_t *zr, bool base16,
                         int32_t *scratch_totals, unsigned long long *bad, hipStream_t st);
 hipError_t launch_stat_sums(const Model &m, const DeviceBuffers &b, const int32_t *zr_now,
                             const int32_t *zr_before, hipStream_t st);
