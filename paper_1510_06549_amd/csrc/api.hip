@@ -127,11 +127,16 @@ public:
     void add(T **p, int64_t count)
     {
         *p = nullptr;
+        if (n_ == kMost) {
+            over_ = true;
+            return;
+        }
         if (count <= 0) count = 1;
         parts_[n_++] = {reinterpret_cast<void **>(p), total_};
         total_ += ((size_t)count * sizeof(T) + 255) / 256 * 256;
     }
     size_t bytes() const { return total_; }
+    bool complete() const { return !over_; }
     void place(void *base) const
     {
         for (int i = 0; i < n_; ++i) *parts_[i].p = static_cast<char *>(base) + parts_[i].at;
@@ -139,6 +144,7 @@ public:
     int alloc(spdp_state *s, const char *what)
     {
         char *base = nullptr;
+        if (over_) return fail(SPDP_E_NOMEM, "more arrays than a list holds for %s", what);
         const int rc = dev_alloc(s, &base, (int64_t)total_, what);
         if (rc == SPDP_OK) place(base);
         return rc;
@@ -149,8 +155,10 @@ private:
         void **p;
         size_t at;
     };
-    Part parts_[24] = {};  // the largest list has 19 arrays
+    static constexpr int kMost = 24;  // the largest list has 19 arrays
+    Part parts_[kMost] = {};
     int n_ = 0;
+    bool over_ = false;
     size_t total_ = 0;
 };
 
@@ -171,6 +179,7 @@ int alloc_counts(spdp_state *s, const Arrays &a, const char *what)
         w.add(&B.fz, 2 * (int64_t)m.G * m.Kp);
         w.add(&B.order_len, m.D);
     }
+    if (!a.complete()) return fail(SPDP_E_NOMEM, "more arrays than a list holds for %s", what);
     const size_t need = a.bytes() + w.bytes();
     size_t free = 0, total = 0;
     if (entries > 0 && (hipMemGetInfo(&free, &total) != hipSuccess || free / 2 < need)) {
