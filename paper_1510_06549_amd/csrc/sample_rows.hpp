@@ -770,9 +770,11 @@ hipError_t launch_rows_shape(const RowArgs &A, hipStream_t st)
 template <int LANES, bool ASSOC>
 hipError_t launch_rows_lanes(const RowArgs &A, int kpl, hipStream_t st)
 {
+    if constexpr (LANES < 64) {  // (64 lanes hold three topics each at least, see row_shape)
+        if (kpl == 1) return launch_rows_shape<LANES, 1, ASSOC>(A, st);
+        if (kpl == 2) return launch_rows_shape<LANES, 2, ASSOC>(A, st);
+    }
     switch (kpl) {
-    case 1: return launch_rows_shape<LANES, 1, ASSOC>(A, st);
-    case 2: return launch_rows_shape<LANES, 2, ASSOC>(A, st);
     case 3: return launch_rows_shape<LANES, 3, ASSOC>(A, st);
     case 4: return launch_rows_shape<LANES, 4, ASSOC>(A, st);
     case 5: return launch_rows_shape<LANES, 5, ASSOC>(A, st);
@@ -783,7 +785,8 @@ hipError_t launch_rows_lanes(const RowArgs &A, int kpl, hipStream_t st)
     case 12: return launch_rows_shape<LANES, 12, ASSOC>(A, st);
     case 13: return launch_rows_shape<LANES, 13, ASSOC>(A, st);
     case 14: return launch_rows_shape<LANES, 14, ASSOC>(A, st);
-    default: return launch_rows_shape<LANES, 16, ASSOC>(A, st);
+    case 16: return launch_rows_shape<LANES, 16, ASSOC>(A, st);
+    default: return hipErrorInvalidValue;
     }
 }
 

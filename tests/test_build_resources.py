@@ -66,7 +66,9 @@ def test_weight_row_sampler_keeps_its_registers(usage_of, src):
         if m := name.search(n):
             seen[int(m.group(1)), int(m.group(2))] = u
     kpls = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 13, 14, 16}  # topics per lane
-    assert {k for lanes, k in seen} == kpls and {lanes for lanes, k in seen} == {16, 32, 64}
+    # (64 lanes: only for more than 128 topics)
+    assert set(seen) == {(lanes, k) for lanes in (16, 32, 64) for k in kpls
+                         if lanes < 64 or k > 2}
     for (lanes, kpl), u in seen.items():
         # 512 VGPRs a lane of a SIMD, shared by 5, 4 or 3 wavefronts in units of 8
         most = 96 if kpl <= 4 else 128 if kpl <= 13 else 168
