@@ -25,7 +25,9 @@
  *     all its device memory until spdp_destroy().
  *   - Streams: all device work of a state runs in order on the HIP stream given
  *     at creation (NULL = the null stream).  spdp_sweep() only enqueues; calls
- *     that return data to the host synchronise that stream.
+ *     that return data to the host synchronise that stream.  Sweeps may be
+ *     captured into a HIP graph, an even number of them, so that a replay leaves
+ *     the states where the host expects them.
  *   - Threading: a state may be used by one host thread at a time.
  *   - Determinism: results are a pure function of (corpus, groups, K,
  *     hyperparameters, init seed, sequence of (sweep, seed)), independent of
@@ -109,8 +111,8 @@ typedef struct {
  * frequent pair: 17.2 GB at 32767, 68.7 GB at 65535.
  * A state with enough tokens per (group, word) pair also holds weight rows (up
  * to 8 GiB) that make its sweeps faster.  Where device memory is short they are
- * left out, or given back to a later call that needs their memory, and sweeps go
- * on with the same results.
+ * left out, or given back to a later call on the state that needs their memory
+ * (not once a sweep has been captured), and sweeps go on with the same results.
  * On success *out holds the new state; on error *out is NULL.
  */
 int spdp_create(const spdp_corpus *corpus, const spdp_groups *groups, int32_t K, double alpha,

@@ -68,6 +68,9 @@ struct spdp_state {
     // without them
     void *weight_rows = nullptr;
     int64_t weight_bytes = 0;
+    // a sweep of this state has been captured into a graph: its replays read the
+    // weight rows, and change the counts without the flags above
+    bool captured = false;
 };
 
 namespace {
@@ -93,7 +96,7 @@ template <typename T>
 hipError_t work_malloc(const spdp_state *s, T **p, size_t bytes)
 {
     hipError_t e = hipMalloc(p, bytes);
-    if (e == hipSuccess || !s->weight_rows) return e;
+    if (e == hipSuccess || !s->weight_rows || s->captured) return e;
     (void)hipGetLastError();
     drop_weight_rows(const_cast<spdp_state *>(s));  // (no output of the state changes)
     return hipMalloc(p, bytes);
@@ -272,20 +275,34 @@ int rebuild_state(spdp_state *s)
 // estimates, likelihood, fold-in, the asynchronous sweep).
 hipError_t widen_rows(const spdp_state *s)
 {
-    if (s->rows32) return hipSuccess;
+    if (s->rows32 && !s->captured) return hipSuccess;
     hipError_t e = launch_widen(s->m, s->b, s->st);
     if (e == hipSuccess) s->rows32 = true;
     return e;
 }
 
-// The 16-bit copy of the shadow base, once after each rebuild, for the samplers
-// over count rows.
+// Whether the 16-bit copy of the shadow base is that of the counts (a captured
+// sweep over count rows makes it in every replay, one over weight rows never).
+bool base16_current(const spdp_state *s)
+{
+    return s->base16 && (!s->captured || s->m.rows.Kw == 0);
+}
+
+// That copy, once after each rebuild, for the samplers over count rows.
 hipError_t copy_base16(spdp_state *s)
 {
-    if (s->base16) return hipSuccess;
+    if (base16_current(s)) return hipSuccess;
     hipError_t e = launch_base16(s->m, s->b, s->st);
     if (e == hipSuccess) s->base16 = true;
     return e;
+}
+
+void note_capture(spdp_state *s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (s->captured || !s->st) return;  // (the null stream cannot be captured)
+    if (hipStreamIsCapturing(s->st, &c) == hipSuccess && c != hipStreamCaptureStatusNone)
+        s->captured = true;
 }
 
 // The sampling step of one sweep, from the sweep-start counts and constants:
@@ -657,6 +674,7 @@ int spdp_sweep(spdp_state *s, uint32_t sweep, uint64_t seed)
     DeviceBuffers &b = s->b;
     int32_t *zr_old = b.zr[s->cur], *zr_new = b.zr[1 - s->cur];
     int rc;
+    note_capture(s);
     if ((rc = timed(s, 0, [&] { return sample_step(s, zr_old, zr_new, sweep, seed); })) != SPDP_OK)
         return rc;
     // (word associations: source-keyed shadow base)
@@ -683,13 +701,14 @@ int spdp_sweep_async(spdp_state *s, uint32_t sweep, uint64_t seed, int32_t waves
     HIP_TRY(hipSetDevice(s->device));
     DeviceBuffers &b = s->b;
     int rc;
+    note_capture(s);
     if (!b.order) {
         if ((rc = dev_alloc(s, &b.order, m.N, "visiting order")) != SPDP_OK) return rc;
         if ((rc = dev_alloc(s, &b.tok_doc, m.N, "token documents")) != SPDP_OK) return rc;
         if ((rc = dev_alloc(s, &b.cdk, (int64_t)m.D * m.Kp, "document counts")) != SPDP_OK)
             return rc;
         hipError_t e = build_visit_order(m, b, s->st);  // (allocates what it works in)
-        if (e == hipErrorOutOfMemory && s->weight_rows) {
+        if (e == hipErrorOutOfMemory && s->weight_rows && !s->captured) {
             (void)hipGetLastError();
             drop_weight_rows(s);
             e = build_visit_order(m, b, s->st);
@@ -1305,7 +1324,8 @@ int spdp_check(spdp_state *s, int64_t *bad)
     unsigned long long c[4] = {0, 0, 0, 0};
     hipError_t e = launch_fill_u64(s->b.ctr, 4, 0, s->st);
     if (e == hipSuccess)
-        e = launch_check(m, s->b, s->b.zr[s->cur], s->base16, scratch, s->b.ctr, s->st);
+        e = launch_check(m, s->b, s->b.zr[s->cur], base16_current(s), scratch, s->b.ctr,
+                         s->st);
     if (e == hipSuccess) e = hipMemcpyAsync(c, s->b.ctr, sizeof c, hipMemcpyDeviceToHost, s->st);
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);
     (void)hipFree(scratch);

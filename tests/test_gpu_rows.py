@@ -68,6 +68,42 @@ def test_sweeps_with_associations_match_oracle(docs, K, S):
     s.close()
 
 
+@pytest.mark.parametrize("sparse", [False, True])
+def test_captured_sweeps(sparse):
+    """Replays of two captured sweeps, with the calls that read the counts between
+    them and eager sweeps between two, leave what eager sweeps leave."""
+    import torch
+
+    print(f"captured sweeps, {'count' if sparse else 'weight'} rows", flush=True)
+    cp = _corpus(450, 60, 60)
+    if sparse:
+        cp = _sparse(cp, 6000, 3)
+    args = (cp.words, cp.doc_off, cp.doc_group, cp.n_groups, cp.vocab, 60, 0.1, 0.5, 20.0, 0.01)
+    stream = torch.cuda.Stream()
+    s, e = sp.Sampler(*args, hip_stream=stream.cuda_stream), sp.Sampler(*args)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        s.sweep(0, 7)
+        s.sweep(1, 7)
+    for rep in range(3):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        e.sweep(0, 7)
+        e.sweep(1, 7)
+        for got, want in zip(parity.state_of(s, None), parity.state_of(e, None)):
+            assert np.array_equal(got, want), rep
+        for got, want in zip(s.counts() + s.totals(), e.counts() + e.totals()):
+            assert np.array_equal(got, want), rep
+        for got, want in zip(s.conditionals(9, 7, 0, 99), e.conditionals(9, 7, 0, 99)):
+            assert np.array_equal(got, want), rep
+        assert s.check() == 0
+        for x in (s, e) if rep == 1 else ():
+            x.sweep(2, 7)
+            x.sweep(3, 7)
+    s.close()
+    e.close()
+
+
 EXTREMES = [(0.1, 20.0, 0.01), (1e38, 20.0, 0.01), (1e300, 20.0, 0.01), (1e-310, 20.0, 0.01),
             (0.1, 1e-40, 0.01), (0.1, 1e300, 0.01), (0.1, 20.0, 1e-25), (0.1, 20.0, 1e300)]
 
