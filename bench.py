@@ -55,12 +55,16 @@ def narrow_fraction(cp) -> float:
     return float(np.mean(c[q] <= 255)) if len(q) else 0.0
 
 
-def used_rows(cp) -> int:
-    """(group, word) pairs that have tokens."""
+def used_rows(cp, lens=None):
+    """(group, word) pairs that have tokens: their number, the number of those with at
+    most 255 tokens, and (lens: length of each row's source list) their mean length."""
     import numpy as np
 
     q = np.repeat(cp.doc_group, np.diff(cp.doc_off)).astype(np.int64) * cp.vocab + cp.words
-    return int(np.count_nonzero(np.bincount(q)))
+    c = np.bincount(q)
+    used = np.flatnonzero(c)
+    sources = 1.0 if lens is None or not len(used) else float(lens[used].mean())
+    return len(used), int(np.count_nonzero(c[used] <= 255)), sources
 
 
 def sample_bytes_per_token(K: int, wide: bool, narrow: float = 0.0) -> float:
@@ -73,11 +77,21 @@ def sample_bytes_per_token(K: int, wide: bool, narrow: float = 0.0) -> float:
     return (4 - 2 * narrow) * K + (4 if wide else 2) * K + 13
 
 
-def weight_row_bytes_per_token(K: int, n_tokens: int, rows_used: int) -> float:
+def weight_row_bytes_per_token(K: int, n_tokens: int, rows_used: int, rows_narrow: int,
+                               sources: float = 1.0) -> float:
     """The same for a sweep over weight rows: the K fp32 weights of the token's
     row and the token stream, and per row with tokens, once a sweep, its packed
-    counts and shadow-base counts in and two fp32 values per topic out."""
-    return 4 * K + 13 + 16 * K * rows_used / max(n_tokens, 1)
+    counts (16-bit cells in the narrow rows), one int32 shadow-base row per source
+    (one without associations) and two fp32 values per topic out."""
+    per_sweep = K * (rows_used * (12 + 4 * sources) - 2 * rows_narrow)
+    return 4 * K + 13 + per_sweep / max(n_tokens, 1)
+
+
+def weight_row_assoc_bytes_per_token(mean_sources: float, Sp: int) -> float:
+    """What a token over weight rows needs besides with word associations: its
+    row's source record and the sources' base counts of its own topic (those of the
+    drawn topic, for a head, are not counted)."""
+    return 8 * Sp + 4 * mean_sources
 
 
 def assoc_bytes_per_token(K: int, wide: bool, mean_sources: float, Sp: int,
@@ -124,22 +138,27 @@ def shadow_base_wide(s) -> bool:
 
 def kernel_source_hash(kernel: str) -> str:
     """SHA-256 of what a sampling kernel is compiled from: its own file, the
-    two headers that file includes, then the file's compiler flags."""
+    headers that file includes, then the file's compiler flags."""
     import hashlib
 
     from paper_1510_06549_amd import build_lib
 
     csrc = os.path.join(ROOT, "paper_1510_06549_amd", "csrc")
-    source = {"k_sample": "sample.hip", "k_sample_assoc": "sample_assoc.hip"}[kernel]
+    source, own = {"k_sample": ("sample.hip", ()),
+                   "k_sample_assoc": ("sample_assoc.hip", ()),
+                   "k_sample_rows": ("sample_rows.hip", ("sample_rows.hpp",)),
+                   "k_sample_rows_assoc": ("sample_rows.hip", ("sample_rows_assoc.hip",
+                                                               "sample_rows.hpp"))}[kernel]
     h = hashlib.sha256()
-    for name in (source, "sampler_common.hpp", "spdp_internal.hpp"):
+    for name in (source, *own, "sampler_common.hpp", "spdp_internal.hpp"):
         h.update(open(os.path.join(csrc, name), "rb").read())
     h.update(" ".join(build_lib.source_flags(source)).encode())
     return h.hexdigest()
 
 
 def recorded_traffic(kernel: str, workload: str):
-    """HBM bytes per launch of the sampling kernel measured with rocprofv3
+    """HBM bytes per launch of the sampling kernel (over weight rows, of a sweep's
+    k_weights and k_sample_rows together) measured with rocprofv3
     counters, if they were taken on the current source of that kernel
     (profiles/traffic_<kernel>_<workload>.txt holds the figure with
     kernel_source_hash() at the time), else None."""
@@ -531,8 +550,9 @@ def main():
         traffic = None
     elif weight_rows and assoc is None:
         narrow = narrow_fraction(cp)
-        bpt = weight_row_bytes_per_token(wl.K, N, used_rows(cp))
-        traffic = None
+        rows, rows_narrow, _ = used_rows(cp)
+        bpt = weight_row_bytes_per_token(wl.K, N, rows, rows_narrow)
+        traffic = recorded_traffic("k_sample_rows", wl.name)
     elif assoc is None:
         narrow = narrow_fraction(cp)
         bpt = sample_bytes_per_token(wl.K, wide, narrow)
@@ -546,9 +566,12 @@ def main():
         narrow = narrow_fraction(cp)
         bpt = assoc_bytes_per_token(wl.K, wide, mean_sources, Sp, narrow)
         if weight_rows:
-            bpt = weight_row_bytes_per_token(wl.K, N, used_rows(cp)) + 8 * Sp
-        traffic = (recorded_traffic("k_sample_assoc", f"{wl.name}-assoc{args.assoc}")
-                   if args.assoc_eps == 0.3 and not weight_rows else None)
+            rows, rows_narrow, row_sources = used_rows(cp, lens)
+            bpt = (weight_row_bytes_per_token(wl.K, N, rows, rows_narrow, row_sources)
+                   + weight_row_assoc_bytes_per_token(mean_sources, Sp))
+        traffic = (recorded_traffic("k_sample_rows_assoc" if weight_rows else "k_sample_assoc",
+                                    f"{wl.name}-assoc{args.assoc}")
+                   if args.assoc_eps == 0.3 else None)
     alg = N * bpt
     achieved = alg / avg_sample_s / 1e9
     roofline = {
@@ -564,7 +587,8 @@ def main():
         "traffic_unit": "GB per launch",
         "alg_bytes_per_launch_GB": round(alg / 1e9, 3),
         "bytes_per_token": round(bpt, 2),
-        "shadow_base_bits": 32 if wide else 16,
+        # (the width of the base rows that the token loop reads: none over weight rows)
+        "shadow_base_bits": None if weight_rows else 32 if wide else 16,
         "avg_launch_ms": round(avg_sample_s * 1000.0, 3),
     }
     if args.async_sweep:
