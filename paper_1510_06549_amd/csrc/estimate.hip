@@ -141,11 +141,11 @@ struct PhiArgs {
 // takes one topic of kPhiWords words, so that every divisor and its reciprocal
 // are computed once for them and their loads are in flight together: per value
 // one cell read (a narrow row's 16-bit copy), a few fp64 operations and the
-// write, which bounds the kernel.  blockDim.x topics, blockDim.y runs of words
+// write.  blockDim.x topics, blockDim.y runs of words
 // a block; the groups are outside (grid z), so that writes run along words.
-// 10 groups, 50 000 words, 200 topics: 309 us for phi0 and phi (2.6 TB/s written);
-// 33 us and 389 us when every
-// value took three divisions and a 64-bit division of its index.
+// 10 groups, 50 000 words, 200 topics: 309 us for phi0 and phi (2.8 TB/s written,
+// where a fill reaches 6.3); 33 us and 389 us when every value took three
+// divisions and a 64-bit division of its index.
 constexpr int kPhiWords = 8, kPhiBlock = 1024;
 template <bool ASSOC, bool RECIP>
 __global__ void __launch_bounds__(kPhiBlock) k_phi(PhiArgs A)
