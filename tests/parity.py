@@ -11,6 +11,8 @@ The comparison protocol, per sweep, from one identical state:
         normalised CDF boundary between the two outcomes;
   (iv)  after update and repair the library's state and counts equal the
         oracle's rebuild and repair of the library's sampled (z, r).
+The weights of (ii) are the trace's, which runs the samplers over count rows;
+where the sweep itself is over weight rows, (iv) holds its draws to the same ones.
 With word associations the state is (z, r, source slot), the outcomes per
 token are K (S + 1) and every token draws (the sole head redraws its source).
 """

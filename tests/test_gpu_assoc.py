@@ -160,8 +160,8 @@ def test_topic_counts_and_list_lengths(K, smax):
 
 def test_shadow_base_counts_beyond_16_bits():
     """66 000 distinct words, each listing source 0 only, all seated as heads of
-    topic 0: every head has source 0, so B[0][0] = 66 000 and the sampler reads
-    the 32-bit shadow-base rows."""
+    topic 0: every head has source 0, so B[0][0] = 66 000 and the traced sampler
+    reads the 32-bit shadow-base rows (the sweep's weight rows are made from them)."""
     say("associations: shadow-base count beyond 16 bits")
     V = 66000
     words = np.arange(V, dtype=np.int32)

@@ -2,8 +2,9 @@
 tokens, K = 500, four sources per word, as `bench.py --assoc 4` runs it):
   * counts: totals, the source-keyed shadow base and the count rows of two
     whole groups equal the oracle's rebuild of the library's state;
-  * sampling: weights, uniforms and draws of 40 documents at the start, middle
-    and end of the corpus one by one, and the draws (topic, table indicator
+  * sampling: weights, uniforms and draws (of the trace, over count rows) of 40
+    documents at the start, middle
+    and end of the corpus one by one, and the sweep's own draws (topic, table indicator
     and source slot) of 6 000 whole documents against the oracle's sampling
     step;
   * update and repair: the library's state after the sweep equals the

@@ -266,7 +266,8 @@ def test_narrow_and_wide_rows_at_every_lane_layout(K):
     """Rows of both widths in one corpus: words repeated more than 255 times in
     a group (32-bit rows) beside rare words (16-bit narrow copies), including
     a pair with exactly 255 tokens (the last narrow count) and one with 256,
-    at every per-lane topic count of the sampler."""
+    at every per-lane topic count of the traced sampler over count rows (the
+    sweeps are over weight rows)."""
     say(f"narrow and wide count rows, K = {K}")
     rng = np.random.default_rng(K)
     V = 40
@@ -291,6 +292,37 @@ def test_narrow_and_wide_rows_at_every_lane_layout(K):
         rep, ch, rp = parity.one_step(s, m, sw, 17)
         say(f"  {rep}")
     assert s.check() == 0
+    s.close()
+
+
+@pytest.mark.parametrize("sources", [0, 1, 2, 4, 8])
+@pytest.mark.parametrize("K", [60, 65, 129, 257, 513, 769])
+def test_sweeps_over_count_rows_at_every_lane_layout(K, sources):
+    """The sweep's own instances over count rows, 1 to 16 topics per lane and every
+    length of source record: rows of both widths, and enough words that occur once for
+    the state to go without weight rows."""
+    rng = np.random.default_rng(K + sources)
+    V = 40
+    docs = []
+    for d in range(32):
+        docs.append((d % 2, [0] * 17 + [1] * 15 + list(rng.integers(2, V, size=d))))
+    n = sum(len(d) for _, d in docs)
+    once = -(-24 * n // (K - 24) // 32) + 1  # words of its own in every document
+    for i, (g, d) in enumerate(docs):
+        d += list(V + (i // 2) * once + np.arange(once))
+        rng.shuffle(d)
+    V += 16 * once
+    say(f"count rows, K = {K}, sources {sources}, {n + 32 * once} tokens")
+    cp = corpus_from_docs(docs, vocab=V)
+    c = np.bincount(np.repeat(cp.doc_group, np.diff(cp.doc_off)).astype(np.int64) * V + cp.words)
+    assert c[0] == c[V] == 272 and c[1] == c[V + 1] == 240
+    assoc = synth.associations(2, V, sources, 0.3 if sources > 1 else 0.0, 5) if sources else None
+    s, m = parity.make_pair(cp, W(K=K), init_seed=K, assoc=assoc)
+    for sw in range(2):
+        rep, ch, rp = parity.one_step(s, m, sw, 17)
+        say(f"  {rep}")
+    assert s.check() == 0
+    assert base_copies(s, 2, 17) == 1
     s.close()
 
 

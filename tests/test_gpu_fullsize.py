@@ -5,8 +5,9 @@ The oracle cannot run a whole sweep of this size in test time, so:
   * counts: the library's totals, shadow base and the count rows of two whole
     groups equal the oracle's rebuild of the library's state, bit for bit;
   * sampling: for documents sampled at the start, middle and end of the corpus
-    the library's weights, uniforms and draws are compared with the oracle's
-    one by one (same protocol as the small workloads), and the draws of 30 000
+    the library's weights and uniforms (of the trace, over count rows) and draws
+    are compared with the oracle's
+    one by one (same protocol as the small workloads), and the sweep's own draws of 30 000
     whole documents (7.5 M tokens) with the oracle's sampling step;
   * update and repair: the library's state after the sweep equals the
     oracle's rebuild and repair of the library's sampled (pre-repair) state,

@@ -5,7 +5,7 @@ where the oracle can sample the whole sweep in test time:
   * sampling: every token's sampled (z, r) equals the oracle's sampling step
     on the same state, seed and sweep (>= 99.99 % required; identical in
     practice), and for documents at the start, middle and end of the corpus
-    the weights and uniforms are compared one by one;
+    the weights and uniforms (of the trace, over count rows) are compared one by one;
   * update and repair: the library's state and totals after the sweep equal
     the oracle's rebuild and repair of the library's sampled state.
 Each step prints what it runs before touching the GPU.
